@@ -630,6 +630,9 @@ int create_in(int nx, int ny, int nz, double lx, double ly, double lz, int bc_y,
     h.ps = L.ps;
     h.dx = lx / nx; h.dy = ly / ny; h.dz = lz / nz;
     h.idx = 1.0 / h.dx; h.idy = 1.0 / h.dy; h.idz = 1.0 / h.dz;
+    h.qx = 0.25 * h.idx; h.qy = 0.25 * h.idy; h.qz = 0.25 * h.idz;
+    h.idx2 = h.idx * h.idx; h.idy2 = h.idy * h.idy; h.idz2 = h.idz * h.idz;
+    h.e2x = 1e-6 * h.dx * h.dx; h.e2y = 1e-6 * h.dy * h.dy; h.e2z = 1e-6 * h.dz * h.dz;
     h.y0 = bc_y == EVP_WALLS ? -0.5 * ly : 0.0;
     h.rho = 1.0; h.inv_rho = 1.0; h.lam = 1.0; h.inv_lam = 1.0; h.L2 = 1e4;
     h.a_fene = h.L2 / (h.L2 - 3.0);

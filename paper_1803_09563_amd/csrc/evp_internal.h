@@ -31,6 +31,7 @@ struct Desc {
     long long ncell;             // nx*ny*nz
     long long ps;                // element stride between planes of B, RT, RU (256-byte padded)
     double dx, dy, dz, idx, idy, idz, y0;
+    double qx, qy, qz, idx2, idy2, idz2, e2x, e2y, e2z;   // 1/(4h), 1/h^2 and 1e-6 h^2 per direction
     double rho, inv_rho, mu_s, mu_p, lam, inv_lam, G, tau_y, L2, a_fene;
     double force_amp, force_ky;
     double u_bot, u_top, w_bot, w_top;
@@ -78,6 +79,9 @@ struct Side { hipStream_t s; hipEvent_t fork, join; };
 hipError_t launch_predictor_zm(const Batch& b, int precision, int nx, int ny, int nz, bool freeze,
                                hipStream_t s, bool walls, int model, bool rk3, bool houc,
                                bool two_phase, const Side* side = nullptr);
+// the FP64 predictor with asynchronously staged planes (k_predictor_async.hip)
+hipError_t launch_predictor_async(const Batch& b, int nx, int ny, int nz, bool freeze, hipStream_t s,
+                                  int model, bool rk3, bool houc);
 // two-phase path (k_two_phase.hip)
 hipError_t launch_level_set_stage(const Batch& b, int nx, int ny, int nz, bool walls, bool reinit,
                                   int stage, hipStream_t s);

@@ -1,5 +1,7 @@
 // Predictor of the Adams-Bashforth step (Sec. 3.2.2, Eqs. (rt), (ab2tau), (ru), (ab2)) -- or of
-// one Runge-Kutta substep (Sec. 3.3.1) -- as a z-marching LDS-tiled kernel laid out for CDNA4:
+// one Runge-Kutta substep (Sec. 3.3.1) -- in the mixed form (FP32 stresses), and of the stress part
+// of the two-phase step (FP64), as a z-marching LDS-tiled kernel laid out for CDNA4 (the single-phase
+// FP64 predictor is k_predictor_async.hip):
 //   * a block of 32 x 8 threads owns a 32 x 8 column of cells and marches along z over a chunk of
 //     planes, so every field is read from HBM about once;
 //   * the seven planes k-3..k+3 that the z-direction WENO needs for the thread's own cell live in
@@ -592,25 +594,12 @@ __global__ __launch_bounds__(NTH, (sizeof(T) == 4 && !WALLS) ? 4 : 2) void k_pre
     pred_block<T, WALLS, MODEL, RK3, HOUC, TWOPH>(S, B, freeze, kc, rows, blockIdx.x);
 }
 
-// FP64 channel: the rows next to the walls and the interior tile rows (periodic-in-y code) in one
-// grid, the first n_wall blocks the wall rows (the heavier blocks start first), the rest the
-// interior.  Both parts run two blocks per CU and take the same planes per block, so the blocks
-// of both parts share the rounds instead of the wall rows running after the interior.
-template <int MODEL, bool RK3, bool HOUC>
-__global__ __launch_bounds__(NTH, 2) void k_pred_zm_channel(Batch B, int freeze, int kc, Rows rows_int, Rows rows_wall, int n_wall)
-{
-    __shared__ Smem<double> S;
-    if ((int)blockIdx.x < n_wall) pred_block<double, true, MODEL, RK3, HOUC, false>(S, B, freeze, kc, rows_wall, blockIdx.x);
-    else pred_block<double, false, MODEL, RK3, HOUC, false>(S, B, freeze, kc, rows_int, blockIdx.x - n_wall);
-}
-
 }  // namespace
 
 // planes per block: `target` blocks per grid in total (EVP_PRED_BLOCKS overrides it), at least 4
-// planes per block.  Measured on one MI355X (blocks resident at once: two per CU for FP64, four
-// for the FP32 periodic kernel): periodic grids run best with about one round of resident blocks
-// (512 FP64, 1024 FP32), channels with about four rounds (2048), whose shorter z-chunks leave a
-// shorter last round
+// planes per block.  Measured on one MI355X (the FP32 periodic kernel keeps four blocks per CU
+// resident): periodic grids run best with about one round of resident blocks (1024), channels with
+// about two (2048), whose shorter z-chunks leave a shorter last round
 int predictor_chunk_tiles(int tiles, int nz, int target)
 {
     static const int target_env = [] {
@@ -628,6 +617,7 @@ hipError_t launch_predictor_zm(const Batch& b, int precision, int nx, int ny, in
                                hipStream_t s, bool walls, int model, bool rk3, bool houc,
                                bool two_phase, const Side* side)
 {
+    if (precision == EVP_FP64 && !two_phase) return launch_predictor_async(b, nx, ny, nz, freeze, s, model, rk3, houc);
     const int ntx = (nx + TX - 1) / TX, nty = (ny + TY - 1) / TY;
     // Channel: tile rows whose whole stencil (B rows j0-3 .. j0+TY+2, velocity rows j0-1 ..
     // j0+TY) lies in rows 0 .. ny-3 never see a ghost row or the top wall face; they run the
@@ -645,37 +635,10 @@ hipError_t launch_predictor_zm(const Batch& b, int precision, int nx, int ny, in
         if (in_hi > in_lo) parts[np++] = {true, {0, nty - (in_hi - in_lo), in_lo, in_hi - in_lo}};
         else parts[np++] = {true, {0, nty, 1 << 30, 0}};
     }
-    // FP64 channels run both parts in one grid (k_pred_zm_channel).  In the mixed form the rows
-    // next to the walls run beside the interior on the side stream (measured faster for
-    // 256x128x128 and 512x256x256 channels: the FP32 wall and interior kernels differ in
-    // occupancy, so one grid would run both at the wall kernel's).  The two-phase mode launches
-    // the parts one after the other.
-    if (np == 2 && precision == EVP_FP64 && !two_phase) {
-        // one grid for both parts, chunked over all tile rows (see k_pred_zm_channel)
-        const int kc = predictor_chunk_tiles(ntx * nty, nz, 2048);
-        const int nch = (nz + kc - 1) / kc;
-        const int n_int = ntx * parts[0].rows.count * nch, n_wall = ntx * parts[1].rows.count * nch;
-        dim3 grid(n_int + n_wall, b.count);
-#define EVP_LAUNCH_C(MM, RR)                                                                       \
-    do {                                                                                           \
-        if (houc) hipLaunchKernelGGL((k_pred_zm_channel<MM, RR, true>), grid, dim3(NTH), 0, s, b, fz, kc, parts[0].rows, parts[1].rows, n_wall); \
-        else hipLaunchKernelGGL((k_pred_zm_channel<MM, RR, false>), grid, dim3(NTH), 0, s, b, fz, kc, parts[0].rows, parts[1].rows, n_wall); \
-    } while (0)
-#define EVP_LAUNCH_CR(MM)                                                                          \
-    do {                                                                                           \
-        if (rk3) EVP_LAUNCH_C(MM, true);                                                           \
-        else EVP_LAUNCH_C(MM, false);                                                              \
-    } while (0)
-        switch (model) {
-        case EVP_FENE_P: EVP_LAUNCH_CR(EVP_FENE_P); break;
-        case EVP_SARAMITO: EVP_LAUNCH_CR(EVP_SARAMITO); break;
-        case EVP_NEO_HOOKEAN: EVP_LAUNCH_CR(EVP_NEO_HOOKEAN); break;
-        default: EVP_LAUNCH_CR(EVP_OLDROYD_B); break;
-        }
-#undef EVP_LAUNCH_CR
-#undef EVP_LAUNCH_C
-        return hipGetLastError();
-    }
+    // In the mixed form the rows next to the walls run beside the interior on the side stream
+    // (measured faster for 256x128x128 and 512x256x256 channels: the FP32 wall and interior kernels
+    // differ in occupancy, so one grid would run both at the wall kernel's).  The two-phase mode
+    // launches the parts one after the other.
     const bool fork = np == 2 && side != nullptr && precision == EVP_MIXED;
     if (fork) {
         hipError_t e = hipEventRecord(side->fork, s);
@@ -722,10 +685,8 @@ hipError_t launch_predictor_zm(const Batch& b, int precision, int nx, int ny, in
     }
         if (pw) { EVP_TP_BY_MODEL(true) } else { EVP_TP_BY_MODEL(false) }
 #undef EVP_TP_BY_MODEL
-    } else if (precision == EVP_MIXED) {
-        if (pw) { EVP_BY_MODEL(float, true) } else { EVP_BY_MODEL(float, false) }
     } else {
-        if (pw) { EVP_BY_MODEL(double, true) } else { EVP_BY_MODEL(double, false) }
+        if (pw) { EVP_BY_MODEL(float, true) } else { EVP_BY_MODEL(float, false) }
     }
     }
     if (fork) {

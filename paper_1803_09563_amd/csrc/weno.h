@@ -11,9 +11,8 @@ namespace evp {
 __device__ __forceinline__ double fast_rcp(double a)
 {
     double x = __builtin_amdgcn_rcp(a);
-    x = fma(x, fma(-a, x, 1.0), x);
-    x = fma(x, fma(-a, x, 1.0), x);
-    return x;
+    const double e = fma(-a, x, 1.0);
+    return fma(x, fma(e, e, e), x);
 }
 __device__ __forceinline__ float fast_rcp(float a)
 {
