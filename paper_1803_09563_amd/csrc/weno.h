@@ -7,7 +7,9 @@
 
 namespace evp {
 
-// reciprocal to full precision: hardware estimate refined by Newton steps (x <- x (2 - a x))
+// reciprocal to full precision.  FP64: the hardware estimate (measured |1 - a x| <= 2^-24.4 over
+// 2^-300 .. 2^300) refined by one third-order step, x <- x (1 + e + e^2), e = 1 - a x: 2^-53, as two
+// Newton steps give, with one operation less.  FP32: one Newton step (x <- x (2 - a x)).
 __device__ __forceinline__ double fast_rcp(double a)
 {
     double x = __builtin_amdgcn_rcp(a);
