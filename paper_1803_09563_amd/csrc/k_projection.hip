@@ -430,93 +430,9 @@ __global__ __launch_bounds__(NT) void k_solve_periodic(Batch B)
 // ---------------------------------------------------------------------------------------------
 // walls: tridiagonal solve in y for every (kx, kz), pivots precomputed per (kx, |kz|)
 // ---------------------------------------------------------------------------------------------
-constexpr int TH_NT = 64;   // one wave per block: modes are few, spread them over all CUs
-// TH_P: rows loaded ahead of the dependent recurrence
-template <int TH_P>
-__global__ __launch_bounds__(TH_NT) void k_thomas(Batch B)
-{
-    const Desc& D = *B.d[blockIdx.y];
-    const int nh = D.nh, sh = D.sh, ny = D.ny, nz = D.nz;
-    // lanes run over the padded rows, so each wave's modes start on a 128-byte line
-    const int col = blockIdx.x * TH_NT + threadIdx.x;
-    const int kz = col / sh, kx = col - kz * sh;
-    if (kz >= nz || kx >= nh) return;
-    const int kzs = kz <= nz - kz ? kz : nz - kz;
-    const gptr<const double> __restrict__ piv = (gptr<const double>)D.piv + (long long)kzs * ny * sh + kx;
-    const gptr<double2> __restrict__ s = (gptr<double2>)D.spec + (long long)kz * ny * sh + kx;
-    const double a = D.idy * D.idy;                  // sub- and super-diagonal 1/dy^2
-    const double scale = 1.0 / ((double)D.nx * nz);  // inverse x and z transforms
-    // From row jc on (up to row ny-2) the pivot recurrence of every mode of this wave has reached
-    // its fixed point in floating point: those rows use the mode's pivot of row ny-2, loaded once,
-    // instead of a load per row (the same numbers)
-    const int jc = ((gptr<const int>)D.pvj)[blockIdx.x];
-    const double pinf = ny >= 2 ? piv[(long long)(ny - 2) * sh] : 0.0;
-    auto pivot = [&](int jj) {
-        double pv = pinf;
-        if (jj < jc || jj == ny - 1) pv = piv[(long long)jj * sh];
-        return pv;
-    };
-    // forward sweep d'_j = (r_j - a d'_{j-1}) / (b_j - a c'_{j-1}); the loads of the next block
-    // of TH_P rows are issued before the dependent updates of the current one
-    double2 dp = make_double2(0.0, 0.0);
-    double2 r[TH_P], rn[TH_P];
-    double iv[TH_P], ivn[TH_P];
-    auto fload = [&](int j0, double2* rr, double* ii) {
-#pragma unroll
-        for (int m = 0; m < TH_P; ++m) {
-            const int jj = min(j0 + m, ny - 1);
-            rr[m] = gload2(s + (long long)jj * sh);
-            ii[m] = pivot(jj);
-        }
-    };
-    fload(0, r, iv);
-    for (int j0 = 0; j0 < ny; j0 += TH_P) {
-        if (j0 + TH_P < ny) fload(j0 + TH_P, rn, ivn);
-#pragma unroll
-        for (int m = 0; m < TH_P; ++m) {
-            if (j0 + m < ny) {
-                dp = make_double2((scale * r[m].x - a * dp.x) * iv[m], (scale * r[m].y - a * dp.y) * iv[m]);
-                gstore2(s + (long long)(j0 + m) * sh, dp);
-            }
-        }
-#pragma unroll
-        for (int m = 0; m < TH_P; ++m) { r[m] = rn[m]; iv[m] = ivn[m]; }
-    }
-    // backward sweep x_j = d'_j - c'_j x_{j+1}, c'_j = a / (b_j - a c'_{j-1}); the (0, 0) mode
-    // also sums its profile for the zero-mean gauge
-    double2 x = dp;
-    double sum = dp.x;
-    auto bload = [&](int j1, double2* dd, double* cc) {
-#pragma unroll
-        for (int m = 0; m < TH_P; ++m) {
-            const int jj = max(j1 - m, 0);
-            dd[m] = gload2(s + (long long)jj * sh);
-            cc[m] = a * pivot(jj);
-        }
-    };
-    if (ny >= 2) bload(ny - 2, r, iv);
-    for (int j1 = ny - 2; j1 >= 0; j1 -= TH_P) {
-        if (j1 - TH_P >= 0) bload(j1 - TH_P, rn, ivn);
-#pragma unroll
-        for (int m = 0; m < TH_P; ++m) {
-            if (j1 - m >= 0) {
-                x = make_double2(r[m].x - iv[m] * x.x, r[m].y - iv[m] * x.y);
-                gstore2(s + (long long)(j1 - m) * sh, x);
-                sum += x.x;
-            }
-        }
-#pragma unroll
-        for (int m = 0; m < TH_P; ++m) { r[m] = rn[m]; iv[m] = ivn[m]; }
-    }
-    // gauge: the volume mean of p is the mean over y of the (0, 0) mode (every other mode has zero
-    // mean over x and z); the inverse x transform subtracts it from p
-    if (kx == 0 && kz == 0) ((gptr<double>)D.gauge)[0] = sum / ny;
-}
-
-// Segmented form of the same solve for ny <= TS_L * TS_SEG: a block holds TS_M modes, and each
-// group of TS_M lanes holds TS_L rows of them in registers (segment w of a block: rows
-// [TS_L w, TS_L w + TS_L)), so the spectrum is read once and written once.  Both sweeps are
-// first-order linear recurrences,
+// A block holds TS_M modes, and each group of TS_M lanes holds TS_L rows of them in registers
+// (segment w of a block: rows [TS_L w, TS_L w + TS_L)), so the spectrum is read once and written
+// once.  Both sweeps are first-order linear recurrences,
 //   forward   d'_j = s r_j iv_j + g_j d'_{j-1},
 //   backward  x_j  = d'_j + g_j x_{j+1}  (j <= ny-2; x_{ny-1} = d'_{ny-1}),  g_j = -a iv_j,
 // with |g_j| <= 1 (diagonally dominant rows).  Each segment runs its rows with a zero
@@ -524,14 +440,15 @@ __global__ __launch_bounds__(TH_NT) void k_thomas(Batch B)
 // pairs go through LDS, each segment composes those of the segments before it (after it,
 // backward) into its incoming value, and adds that value times the running product of its
 // coefficients to its rows.  Mathematically the sequential sweep; the sums are associated
-// differently.  At 512x256x256 this takes the solve from 208 to 96 us.  Blocks of 256 threads
-// (16 modes) let three of them share a CU at the kernel's 166 registers; 32 modes (two per CU)
-// took 114 us, 8 modes 99 us.
+// differently.  Against one lane per mode sweeping sequentially (the spectrum read and written
+// twice, a chain of 2 ny dependent steps in few waves): 208 -> 96 us at 512x256x256, 82 -> 15 us at
+// 96x400x64.  Up to 256 rows, blocks of 16 modes (256 threads) let three of them share a CU at the
+// kernel's 166 registers; 32 modes (two per CU) took 114 us, 8 modes 99 us.  Taller channels take 8
+// modes (128 contiguous bytes of a row) in up to 64 segments, 512 threads at 1024 rows.
 constexpr int TS_L = 16;     // rows per lane
-constexpr int TS_M = 16;     // modes per block: 256 contiguous bytes of a row per segment
-constexpr int TS_SEG = 16;   // segments per block at most: 256 threads, ny <= 256
 constexpr int kRawWord3 = 0x00020000;   // raw-buffer format word of CDNA: 32-bit data, no swizzle
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+template <int TS_M, int TS_SEG>   // modes per block, segments per block at most
 __global__ __launch_bounds__(TS_M * TS_SEG) void k_thomas_seg(Batch B)
 {
     __shared__ double fwd[3][TS_SEG][TS_M];    // forward: product, last d'.x, last d'.y
@@ -545,18 +462,23 @@ __global__ __launch_bounds__(TS_M * TS_SEG) void k_thomas_seg(Batch B)
     const int col = blockIdx.x * TS_M + lane;
     const int kz = col / sh, kx = col - kz * sh;
     const bool live = kz < nz && kx < nh;
-    const int kzc = live ? kz : 0;
+    const int kzc = live ? kz : 0, kzr = live ? kz - (TS_SEG > 16 ? (blockIdx.x * TS_M) / sh : 0) : 0;
     const int kzs = kzc <= nz - kzc ? kzc : nz - kzc;
     const double a = D.idy * D.idy;
     const double scale = 1.0 / ((double)D.nx * nz);
-    // converged pivots from row jc on (up to row ny-2), as in k_thomas; jc is kept per 64 modes
+    // From row jc on (up to row ny-2) the pivot recurrence of every mode of these 64 has reached its
+    // fixed point in floating point: those rows use the mode's pivot of row ny-2, loaded once,
+    // instead of a load per row (the same numbers)
     const int jc = ((gptr<const int>)D.pvj)[blockIdx.x * TS_M / 64];
     const int j0 = seg * TS_L;
     // raw buffer accesses: the lane's byte offset of its first row in one register, the row step
     // m sh as the wave-uniform offset (no per-row 64-bit addresses held for the stores)
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((EVP_GLOBAL void*)D.spec, (short)0, 0x7fffffff, kRawWord3);
+    // (offsets from the start of the spectrum up to 256 rows; the taller spectra pass 2^31 bytes, and
+    // count from the plane of the block's first mode)
+    const int kzb = TS_SEG > 16 ? (blockIdx.x * TS_M) / sh : 0;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((EVP_GLOBAL void*)(D.spec + (long long)kzb * ny * sh), (short)0, 0x7fffffff, kRawWord3);
     const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc((EVP_GLOBAL void*)D.piv, (short)0, 0x7fffffff, kRawWord3);
-    const unsigned vs = (unsigned)((((long long)kzc * ny + j0) * sh + kx) * 16);
+    const unsigned vs = (unsigned)((((long long)kzr * ny + j0) * sh + kx) * 16);
     const unsigned vp = (unsigned)((((long long)kzs * ny + j0) * sh + kx) * 8);
     // v: the right-hand side scaled by the row's pivot, then d', then x; g: -a iv_j.  All loads
     // are issued before any is used: a row past ny, a lane past the last mode and a converged
@@ -929,15 +851,13 @@ hipError_t launch_solve_periodic(const Batch& b, int nx, int ny, int nz, hipStre
 hipError_t launch_thomas(const Batch& b, int nx, int ny, int nz, hipStream_t s)
 {
     const int cols = (int)((nx / 2 + 1 + 7) / 8 * 8) * nz;   // padded rows (Desc::sh)
-    if (ny <= TS_L * TS_SEG) {
-        // TS_M lanes per TS_L rows of TS_M modes
-        const int nseg = (ny + TS_L - 1) / TS_L;
-        dim3 grid((cols + TS_M - 1) / TS_M, b.count);
-        hipLaunchKernelGGL(k_thomas_seg, grid, dim3(TS_M * nseg), 0, s, b);
+    const int nseg = (ny + TS_L - 1) / TS_L;
+    if (nseg <= 16) {
+        dim3 grid((cols + 15) / 16, b.count);
+        hipLaunchKernelGGL((k_thomas_seg<16, 16>), grid, dim3(16 * nseg), 0, s, b);
     } else {
-        dim3 grid((cols + TH_NT - 1) / TH_NT, b.count);
-        // 16 rows ahead (248 VGPRs, two waves per SIMD): measured best against 8 and 32
-        hipLaunchKernelGGL(k_thomas<16>, grid, dim3(TH_NT), 0, s, b);
+        dim3 grid((cols + 7) / 8, b.count);
+        hipLaunchKernelGGL((k_thomas_seg<8, 64>), grid, dim3(8 * nseg), 0, s, b);
     }
     return hipGetLastError();
 }
