@@ -488,7 +488,7 @@ int enqueue_two_phase(evp_grid* const* gs, int count, double dt, int nsteps, uns
                 return r;
         }
         if (stop && !freeze) {
-            hipError_t e = evp::launch_copy_ustar(b, nx, ny, nz, true, s);
+            hipError_t e = evp::launch_copy_ustar(b, nx, ny, nz, s);
             if (e != hipSuccess) return hip_fail(e, "copy u*");
         } else if (!freeze) {
             if ((r = timed(g0, EVP_K_SPLIT, [&] { return evp::launch_split_pressure(b, nx, ny, nz, walls, s); }))) return r;
@@ -528,7 +528,7 @@ int enqueue_steps(evp_grid* const* gs, int count, double dt, int nsteps, unsigne
             if (r) return r;
         }
         if (stop && !freeze) {
-            hipError_t e = evp::launch_copy_ustar(b, g0->nx, g0->ny, g0->nz, true, g0->stream);
+            hipError_t e = evp::launch_copy_ustar(b, g0->nx, g0->ny, g0->nz, g0->stream);
             if (e != hipSuccess) return hip_fail(e, "copy u*");
         } else if (!freeze) {
             if ((r = projection(g0, b))) return r;
@@ -913,9 +913,7 @@ int evp_project(evp_grid* g)
     b.count = 1;
     b.d[0] = g->d;
     b.dt[0] = 1.0;
-    b.state[0] = g->parity;
-    hipError_t e = evp::launch_copy_ustar(b, g->nx, g->ny, g->nz, false, g->stream);
-    if (e != hipSuccess) return hip_fail(e, "copy u -> u*");
+    b.state[0] = g->parity | evp::ST_FROM_U;
     const bool prof = g->prof;
     g->prof = false;
     int r = projection(g, b);

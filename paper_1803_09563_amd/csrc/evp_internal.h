@@ -71,6 +71,7 @@ constexpr int ST_PARITY = 1;
 constexpr int ST_EULER = 2;
 constexpr int ST_PZERO = 4;      // two-phase: no pressure history yet (2 p^n - p^{n-1} := 0)
 constexpr int ST_REINIT = 8;     // two-phase: this grid reinitialises its level set now
+constexpr int ST_FROM_U = 16;    // projection of the velocity itself: u takes the place of u*
 
 // Host-side launchers (one per kernel family); shape is common to the whole batch.
 // A second stream with a fork and a join event: work launched there runs beside the main
@@ -107,7 +108,7 @@ hipError_t launch_solve_periodic(const Batch& b, int nx, int ny, int nz, hipStre
 hipError_t launch_thomas(const Batch& b, int nx, int ny, int nz, hipStream_t s);
 hipError_t launch_ifftx(const Batch& b, int nx, int ny, int nz, hipStream_t s);
 hipError_t launch_correct(const Batch& b, int nx, int ny, int nz, hipStream_t s);
-hipError_t launch_copy_ustar(const Batch& b, int nx, int ny, int nz, bool to_u, hipStream_t s);
+hipError_t launch_copy_ustar(const Batch& b, int nx, int ny, int nz, hipStream_t s);
 hipError_t launch_write_fields(const Desc* d, int precision, long long ncell, int ny, int nx,
                                int walls, int parity, const double* u, const double* v,
                                const double* w, const double* B6, const double* hist,

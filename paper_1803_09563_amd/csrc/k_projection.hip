@@ -81,9 +81,10 @@ __global__ __launch_bounds__(NT) void k_div_fftx(Batch B)
     const double sc = D.rho / B.dt[blockIdx.y];
     const int tid = threadIdx.x;
     for (int n = tid; n < N; n += NT) tw[n] = gload2((gptr<const double2>)D.twx + n);
-    const gptr<const double> us = (gptr<const double>)D.us;
-    const gptr<const double> vs = (gptr<const double>)D.vs;
-    const gptr<const double> ws = (gptr<const double>)D.ws;
+    const bool from_u = (B.state[blockIdx.y] & ST_FROM_U) != 0;
+    const gptr<const double> us = (gptr<const double>)(from_u ? D.u : D.us);
+    const gptr<const double> vs = (gptr<const double>)(from_u ? D.v : D.vs);
+    const gptr<const double> ws = (gptr<const double>)(from_u ? D.w : D.ws);
     const gptr<double2> spec = (gptr<double2>)D.spec;
     const int ny = D.ny, nz = D.nz;
     const int nlines = ny * nz;
@@ -197,9 +198,10 @@ __global__ __launch_bounds__(NTP) void k_div_fftxy(Batch B)
         twy[n] = gload2((gptr<const double2>)D.twy + n);
     }
     const double sc = D.rho / B.dt[blockIdx.y];
-    const gptr<const double> us = (gptr<const double>)D.us;
-    const gptr<const double> vs = (gptr<const double>)D.vs;
-    const gptr<const double> ws = (gptr<const double>)D.ws;
+    const bool from_u = (B.state[blockIdx.y] & ST_FROM_U) != 0;
+    const gptr<const double> us = (gptr<const double>)(from_u ? D.u : D.us);
+    const gptr<const double> vs = (gptr<const double>)(from_u ? D.v : D.vs);
+    const gptr<const double> ws = (gptr<const double>)(from_u ? D.w : D.ws);
     const int nz = D.nz;
     const long long sxy = (long long)N * N;
     const double idx = D.idx, idy = D.idy, idz = D.idz;
@@ -661,7 +663,7 @@ __global__ __launch_bounds__(NT) void k_ifftx(Batch B)
 }
 
 // ---------------------------------------------------------------------------------------------
-// velocity correction u = u* - (dt/rho) G_h p; copies between u and u*
+// velocity correction u = u* - (dt/rho) G_h p; copy of u* to u
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_correct(Batch B)
 {
@@ -680,8 +682,9 @@ __global__ __launch_bounds__(256) void k_correct(Batch B)
     const int j = (int)(r % ny), k = (int)(r / ny);
     const double c = B.dt[blockIdx.y] * D.inv_rho;
     const gptr<const double> p = (gptr<const double>)D.p;
-    const gptr<const double> us = (gptr<const double>)D.us, vs = (gptr<const double>)D.vs,
-                             ws = (gptr<const double>)D.ws;
+    const bool from_u = (B.state[blockIdx.y] & ST_FROM_U) != 0;      // in place, cell by cell
+    const gptr<const double> us = (gptr<const double>)(from_u ? D.u : D.us), vs = (gptr<const double>)(from_u ? D.v : D.vs),
+                             ws = (gptr<const double>)(from_u ? D.w : D.ws);
     const gptr<double> u = (gptr<double>)D.u, v = (gptr<double>)D.v, w = (gptr<double>)D.w;
     const double p0 = p[q];
     const double px = p[q - i + (i + 1 == nx ? 0 : i + 1)];
@@ -696,21 +699,16 @@ __global__ __launch_bounds__(256) void k_correct(Batch B)
     }
 }
 
-__global__ __launch_bounds__(256) void k_copy_ustar(Batch B, int to_u)
+__global__ __launch_bounds__(256) void k_copy_ustar(Batch B)
 {
     const Desc& D = *B.d[blockIdx.y];
     const long long ncell = D.ncell;
     const gptr<double> u = (gptr<double>)D.u, v = (gptr<double>)D.v, w = (gptr<double>)D.w;
-    const gptr<double> us = (gptr<double>)D.us, vs = (gptr<double>)D.vs, ws = (gptr<double>)D.ws;
+    const gptr<const double> us = (gptr<const double>)D.us, vs = (gptr<const double>)D.vs, ws = (gptr<const double>)D.ws;
     const long long q = (long long)blockIdx.x * 256 + threadIdx.x;
     if (q >= ncell) return;
-    if (to_u) {
-        const double a = us[q], b = vs[q], c = ws[q];
-        u[q] = a; v[q] = b; w[q] = c;
-    } else {
-        const double a = u[q], b = v[q], c = w[q];
-        us[q] = a; vs[q] = b; ws[q] = c;
-    }
+    const double a = us[q], b = vs[q], c = ws[q];
+    u[q] = a; v[q] = b; w[q] = c;
 }
 
 }  // namespace
@@ -870,11 +868,11 @@ hipError_t launch_correct(const Batch& b, int nx, int ny, int nz, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_copy_ustar(const Batch& b, int nx, int ny, int nz, bool to_u, hipStream_t s)
+hipError_t launch_copy_ustar(const Batch& b, int nx, int ny, int nz, hipStream_t s)
 {
     const long long n = (long long)nx * ny * nz;
     dim3 grid((unsigned)((n + 255) / 256), b.count);
-    hipLaunchKernelGGL(k_copy_ustar, grid, dim3(256), 0, s, b, to_u ? 1 : 0);
+    hipLaunchKernelGGL(k_copy_ustar, grid, dim3(256), 0, s, b);
     return hipGetLastError();
 }
 
