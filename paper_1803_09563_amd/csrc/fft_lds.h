@@ -7,13 +7,17 @@
 
 #include <hip/hip_runtime.h>
 
+// The arithmetic here is written out with explicit fused operations and otherwise not contracted, so
+// that a line's transform has the same bits whatever kernel it is inlined in.
+#pragma clang fp contract(off)
+
 namespace evp {
 
 __device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
 __device__ __forceinline__ double2 cmul(double2 a, double2 b)
 {
-    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+    return make_double2(fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x));
 }
 __device__ __forceinline__ double2 cconj(double2 a) { return make_double2(a.x, -a.y); }
 __device__ __forceinline__ double2 cscale(double2 a, double s) { return make_double2(a.x * s, a.y * s); }
@@ -67,7 +71,7 @@ template <> __device__ __forceinline__ void dft<3>(double2* v)
 {
     const double h3 = 0.86602540378443864676;   // sin(pi/3)
     double2 s = cadd(v[1], v[2]), d = csub(v[1], v[2]);
-    double2 m = make_double2(v[0].x - 0.5 * s.x, v[0].y - 0.5 * s.y);
+    double2 m = make_double2(fma(-0.5, s.x, v[0].x), fma(-0.5, s.y, v[0].y));
     double2 t = make_double2(h3 * d.y, -h3 * d.x);   // -i sin(pi/3) d
     v[0] = cadd(v[0], s);
     v[1] = cadd(m, t);
@@ -91,10 +95,10 @@ template <> __device__ __forceinline__ void dft<5>(double2* v)
     const double s1 = 0.95105651629515357212, s2 = 0.58778525229247312917;
     const double2 a1 = cadd(v[1], v[4]), b1 = csub(v[1], v[4]);
     const double2 a2 = cadd(v[2], v[3]), b2 = csub(v[2], v[3]);
-    const double2 p1 = make_double2(v[0].x + c1 * a1.x + c2 * a2.x, v[0].y + c1 * a1.y + c2 * a2.y);
-    const double2 p2 = make_double2(v[0].x + c2 * a1.x + c1 * a2.x, v[0].y + c2 * a1.y + c1 * a2.y);
-    const double2 q1 = cmi(make_double2(s1 * b1.x + s2 * b2.x, s1 * b1.y + s2 * b2.y));   // -i (s1 b1 + s2 b2)
-    const double2 q2 = cmi(make_double2(s2 * b1.x - s1 * b2.x, s2 * b1.y - s1 * b2.y));   // -i (s2 b1 - s1 b2)
+    const double2 p1 = make_double2(fma(c2, a2.x, fma(c1, a1.x, v[0].x)), fma(c2, a2.y, fma(c1, a1.y, v[0].y)));
+    const double2 p2 = make_double2(fma(c1, a2.x, fma(c2, a1.x, v[0].x)), fma(c1, a2.y, fma(c2, a1.y, v[0].y)));
+    const double2 q1 = cmi(make_double2(fma(s1, b1.x, s2 * b2.x), fma(s1, b1.y, s2 * b2.y)));     // -i (s1 b1 + s2 b2)
+    const double2 q2 = cmi(make_double2(fma(s2, b1.x, -(s1 * b2.x)), fma(s2, b1.y, -(s1 * b2.y))));   // -i (s2 b1 - s1 b2)
     v[0] = cadd(v[0], cadd(a1, a2));
     v[1] = cadd(p1, q1);
     v[4] = csub(p1, q1);
@@ -160,7 +164,71 @@ __device__ __forceinline__ void fft_stages(double2* buf, int es, int t, bool act
     }
 }
 
+// The same transform with its first inputs and its last outputs in registers, so that a line
+// loaded from memory goes through LDS only between stages.  REV: radices in reverse order.  The
+// first stage of radix R takes, from thread t, elements j + r N/R of its butterflies j = t + m T; the
+// last stage of radix R leaves results j + r N/R with the same j: a transform with REV can follow one
+// without on the values in place.
+template <int N, bool REV> constexpr int fft_radix(int s)
+{
+    return make_plan(N).r[REV ? make_plan(N).nst - 1 - s : s];
+}
+// butterflies per thread of a stage of radix R
+template <int N, int T, int R> constexpr int fft_per_thread() { return (N / R + T - 1) / T; }
+
+// Stage S on v; FRESH: no thread still reads buf.  emit(k, x, m, r) takes result k (butterfly m of the
+// thread, output r).
+template <int N, int T, bool REV, int S, int NS, bool FRESH, int MB, int R, typename Emit>
+__device__ __forceinline__ void fft_from(double2 (&v)[MB][R], double2* buf, int es, int t, bool active, const double2* tw, Emit&& emit)
+{
+    static_assert(R == fft_radix<N, REV>(S) && MB == fft_per_thread<N, T, R>(), "the stage's registers");
+    constexpr int NB = N / R;
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+        if (active && (NB % T == 0 || t + m * T < NB)) dft<R>(v[m]);
+    if constexpr (S + 1 == make_plan(N).nst) {
+#pragma unroll
+        for (int m = 0; m < MB; ++m) {
+            const int j = t + m * T;
+            if (active && (NB % T == 0 || j < NB)) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) emit(j + r * NS, v[m][r], m, r);
+            }
+        }
+    } else {
+        if constexpr (!FRESH) __syncthreads();
+#pragma unroll
+        for (int m = 0; m < MB; ++m) {
+            const int j = t + m * T;
+            if (active && (NB % T == 0 || j < NB)) {
+                const int base = (j / NS) * NS * R + (j % NS);
+#pragma unroll
+                for (int r = 0; r < R; ++r) buf[(base + r * NS) * es] = v[m][r];
+            }
+        }
+        __syncthreads();
+        constexpr int R2 = fft_radix<N, REV>(S + 1), NB2 = N / R2, NS2 = NS * R, MB2 = fft_per_thread<N, T, R2>(), TWS = N / (NS2 * R2);
+        double2 w[MB2][R2];
+#pragma unroll
+        for (int m = 0; m < MB2; ++m) {
+            const int j = t + m * T;
+            if (active && (NB2 % T == 0 || j < NB2)) {
+                const int k = j % NS2;
+#pragma unroll
+                for (int r = 0; r < R2; ++r) {
+                    double2 x = buf[(j + r * NB2) * es];
+                    if (r > 0) x = cmul(x, tw[r * k * TWS]);
+                    w[m][r] = x;
+                }
+            }
+        }
+        fft_from<N, T, REV, S + 1, NS2, false>(w, buf, es, t, active, tw, emit);
+    }
+}
+
 // Threads per line used by the transform kernels for length N.
 template <int N> constexpr int fft_threads() { return N >= 8 ? N / 8 : 1; }
 
 }  // namespace evp
+
+#pragma clang fp contract(fast)

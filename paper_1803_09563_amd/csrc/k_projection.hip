@@ -22,48 +22,11 @@ constexpr int NT = 256;    // threads per block of the line-transform kernels
 constexpr int TK = 16;     // consecutive kx per block in the strided passes
 
 __device__ __forceinline__ int wrapi(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
-
-// Strided tile <-> LDS: element e = tid + m NT of the N x TK tile is (row n = e / TK, column
-// c = e % TK).  The column is the same for every m of a thread, so its bounds check is hoisted;
-// loads are issued in groups of up to 16 before their LDS stores.
-template <int N, bool CONJ>
-__device__ __forceinline__ void tile_in(double2* buf, gptr<const double2> __restrict__ src, long long es,
-                                        bool colok, int tid)
+// sc (D_h u*) of a cell from a = u, u(i-1), v, -, w, w(k-1) and vm = v(j-1), in the same operations in
+// every kernel
+__device__ __forceinline__ double divergence(const double* a, double vm, double idx, double idy, double idz, double sc)
 {
-    constexpr int TOT = N * TK, M = (TOT + NT - 1) / NT, G = M < 16 ? M : 16;
-    const int c = tid % TK, n0 = tid / TK;
-#pragma unroll
-    for (int g0 = 0; g0 < M; g0 += G) {
-        double2 v[G];
-#pragma unroll
-        for (int m = 0; m < G; ++m) {
-            const int n = n0 + (g0 + m) * (NT / TK);
-            v[m] = make_double2(0.0, 0.0);
-            if (colok && n < N) v[m] = gload2(src + n * es + c);
-        }
-#pragma unroll
-        for (int m = 0; m < G; ++m) {
-            const int n = n0 + (g0 + m) * (NT / TK);
-            if (n < N) buf[n * TK + c] = CONJ ? cconj(v[m]) : v[m];
-        }
-    }
-}
-
-template <int N, bool CONJ>
-__device__ __forceinline__ void tile_out(const double2* buf, gptr<double2> __restrict__ dst, long long es,
-                                         bool colok, int tid)
-{
-    constexpr int TOT = N * TK, M = (TOT + NT - 1) / NT;
-    const int c = tid % TK, n0 = tid / TK;
-    if (!colok) return;
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-        const int n = n0 + m * (NT / TK);
-        if (n < N) {
-            const double2 x = buf[n * TK + c];
-            gstore2(dst + n * es + c, CONJ ? cconj(x) : x);
-        }
-    }
+    return sc * fma(a[4] - a[5], idz, fma(a[2] - vm, idy, (a[0] - a[1]) * idx));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -92,55 +55,70 @@ __global__ __launch_bounds__(NT) void k_div_fftx(Batch B)
     const int pair0 = blockIdx.x * LP;
     const double idx = D.idx, idy = D.idy, idz = D.idz;
     const long long sxy = (long long)N * ny;
-    // divergence of u* on the block's lines; loads of four elements (24 values) are issued
-    // before their arithmetic and LDS stores
-    constexpr int M = (LP * N + NT - 1) / NT, G = M < 4 ? M : 4;
+    // divergence of u* at the inputs of the thread's first butterflies, on the two lines of its pair;
+    // the loads of up to four elements (48 values) are issued before their arithmetic
     const bool walls = D.walls != 0;
+    const int lp = tid / T, t = tid - (tid / T) * T;
+    const bool active = lp < LP;
+    constexpr int R0 = fft_radix<N, false>(0), NB = N / R0, MB = fft_per_thread<N, T, R0>();
+    long long q0[2];
+    int j0[2], k0[2];
+    bool ok[2];
 #pragma unroll
-    for (int g0 = 0; g0 < M; g0 += G) {
-        double ld[G][2][7];
-        int slot[G];
+    for (int h = 0; h < 2; ++h) {
+        const int l = 2 * (pair0 + lp) + h;
+        ok[h] = active && l < nlines;
+        const int ll = ok[h] ? l : 0;
+        k0[h] = ll / ny;
+        j0[h] = ll - k0[h] * ny;
+        q0[h] = (long long)ll * N;
+    }
+    double2 v[MB][R0];
+    constexpr int G = R0 % 4 == 0 ? 4 : R0;
 #pragma unroll
-        for (int m = 0; m < G; ++m) {
-            const int e = tid + (g0 + m) * NT;
-            const int ee = e < LP * N ? e : 0;
-            const int lp = ee / N, i = ee - lp * N;
-            const int pair = pair0 + lp;
-            slot[m] = (e < LP * N) ? ee : -1;
+    for (int m = 0; m < MB; ++m) {
+        const int jb = t + m * T < NB ? t + m * T : 0;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                int l = 2 * pair + h;
-                const bool ok = pair < npairs && l < nlines;
-                l = ok ? l : 0;
-                const int k = l / ny, j = l - k * ny;
-                const long long q = (long long)l * N + i;
-                ld[m][h][0] = us[q];
-                ld[m][h][1] = us[q - i + wrapi(i - 1, N)];
-                ld[m][h][2] = vs[q];
-                ld[m][h][3] = (j > 0) ? vs[q - N] : vs[q + (long long)(ny - 1) * N];
-                ld[m][h][4] = ws[q];
-                ld[m][h][5] = (k > 0) ? ws[q - sxy] : ws[q + (long long)(nz - 1) * sxy];
-                ld[m][h][6] = (ok ? 1.0 : 0.0) * ((j == 0 && walls) ? 0.0 : 1.0);   // flags
-                if (!ok) ld[m][h][6] = -1.0;
+        for (int g0 = 0; g0 < R0; g0 += G) {
+            double ld[G][2][6];
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const int i = jb + (g0 + g) * NB;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const long long q = q0[h] + i;
+                    ld[g][h][0] = us[q];
+                    ld[g][h][1] = us[q0[h] + wrapi(i - 1, N)];
+                    ld[g][h][2] = vs[q];
+                    ld[g][h][3] = (j0[h] > 0) ? vs[q - N] : vs[q + (long long)(ny - 1) * N];
+                    ld[g][h][4] = ws[q];
+                    ld[g][h][5] = (k0[h] > 0) ? ws[q - sxy] : ws[q + (long long)(nz - 1) * sxy];
+                }
             }
-        }
 #pragma unroll
-        for (int m = 0; m < G; ++m) {
-            if (slot[m] < 0) continue;
-            double r2[2];
+            for (int g = 0; g < G; ++g) {
+                double r2[2];
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const double* a = ld[m][h];
-                const double vm = (a[6] > 0.0) ? a[3] : 0.0;        // wall: v = 0 below row 0
-                const double rr = sc * ((a[0] - a[1]) * idx + (a[2] - vm) * idy + (a[4] - a[5]) * idz);
-                r2[h] = (a[6] < 0.0) ? 0.0 : rr;
+                for (int h = 0; h < 2; ++h) {
+                    const double* a = ld[g][h];
+                    const double vm = (walls && j0[h] == 0) ? 0.0 : a[3];        // wall: v = 0 below row 0
+                    r2[h] = ok[h] ? divergence(a, vm, idx, idy, idz, sc) : 0.0;
+                }
+                v[m][g0 + g] = make_double2(r2[0], r2[1]);
             }
-            buf[slot[m]] = make_double2(r2[0], r2[1]);
         }
     }
+    double2* const line = buf + (active ? lp : 0) * N;
+    constexpr int RL = fft_radix<N, false>(make_plan(N).nst - 1), ML = fft_per_thread<N, T, RL>();
+    double2 z[ML][RL];
+    fft_from<N, T, false, 0, 1, true>(v, line, 1, t, active, tw, [&](int, double2 x, int m, int r) { z[m][r] = x; });
     __syncthreads();
-    const int lp = tid / T, t = tid - (tid / T) * T;
-    fft_stages<N, T, 0, 1>(buf + lp * N, 1, t, lp < LP, tw);
+#pragma unroll
+    for (int m = 0; m < ML; ++m)
+#pragma unroll
+        for (int r = 0; r < RL; ++r)
+            if (active && t + m * T < N / RL) line[t + m * T + r * (N / RL)] = z[m][r];
+    __syncthreads();
     const int sh = D.sh;
     for (int e = tid; e < LP * NHF; e += NT) {
         const int l2 = e / NHF, k = e - l2 * NHF;
@@ -236,7 +214,7 @@ __global__ __launch_bounds__(NTP) void k_div_fftxy(Batch B)
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const double* a = ld[m][h];
-                r2[h] = sc * ((a[0] - a[1]) * idx + (a[2] - a[3]) * idy + (a[4] - a[5]) * idz);
+                r2[h] = divergence(a, a[3], idx, idy, idz, sc);
             }
             buf[e] = make_double2(r2[0], r2[1]);
         }
@@ -351,82 +329,110 @@ __global__ __launch_bounds__(NTP) void k_ifftxy(Batch B)
 // ---------------------------------------------------------------------------------------------
 // strided forward / inverse transform along y (axis 1) or z (axis 2), in place
 // ---------------------------------------------------------------------------------------------
+// A tile is TK consecutive kx of one y or z line bundle, T threads per column; lines so short that a
+// tile has less than a wave take several tiles per block.  A thread loads the inputs of its first
+// butterflies straight into registers and stores its last results from them, so a line passes
+// through LDS only between the stages (one exchange for lengths of two radices, two for three).  Against
+// staging the tile through LDS before and after the transform, with every stage from LDS to LDS:
+// forward y 12.2 -> 11.1 us, solve 19.9 -> 16.8, inverse 14.9 -> 13.5, x inverse 13.7 -> 11.1 at 128^3;
+// forward z 20.0 -> 17.7, inverse z 17.5 -> 17.2, x inverse 20.7 -> 17.2 on the 256 x 128 x 128 channel; no change at 512 x 256 x 256,
+// where each pass is at the rate of memory (93 us for 538 MB).
 template <int N>
 constexpr int strided_threads() { return fft_threads<N>() < NT / TK ? fft_threads<N>() : NT / TK; }
+template <int N>
+constexpr int strided_tiles() { return strided_threads<N>() * TK >= 64 ? 1 : 64 / (strided_threads<N>() * TK); }
+template <int N>
+constexpr int strided_block() { return strided_threads<N>() * TK * strided_tiles<N>(); }
 
 template <int N, bool INV>
-__global__ __launch_bounds__(NT) void k_fft_strided(Batch B, int axis)
+__global__ __launch_bounds__(strided_block<N>()) void k_fft_strided(Batch B, int axis)
 {
-    constexpr int T = strided_threads<N>();
-    __shared__ double2 buf[N * TK];
+    constexpr int T = strided_threads<N>(), NTL = strided_tiles<N>();
+    __shared__ double2 buf[NTL][N * TK];
     __shared__ double2 tw[N];
     const Desc& D = *B.d[blockIdx.y];
     const int tid = threadIdx.x;
     const gptr<const double2> twg = (gptr<const double2>)(axis == 1 ? D.twy : D.twz);
-    const gptr<double2> spec = (gptr<double2>)D.spec;
-    for (int n = tid; n < N; n += NT) tw[n] = gload2(twg + n);
+    for (int n = tid; n < N; n += strided_block<N>()) tw[n] = gload2(twg + n);
     const int nh = D.nh, sh = D.sh, ny = D.ny;
     const int ntk = (nh + TK - 1) / TK;
-    const int tile = blockIdx.x % ntk, other = blockIdx.x / ntk;
-    const int kx0 = tile * TK;
+    const int c = tid % TK, t = (tid / TK) % T, sub = tid / (TK * T);
+    const int id = blockIdx.x * NTL + sub;
+    const int tile = id % ntk, other = id / ntk;
+    const int kx = tile * TK + c;
+    const bool active = kx < nh && other < (axis == 1 ? D.nz : ny);
     long long base, es;
-    if (axis == 1) { base = (long long)other * ny * sh + kx0; es = sh; }
-    else { base = (long long)other * sh + kx0; es = (long long)sh * ny; }
-    const bool colok = kx0 + tid % TK < nh;
-    tile_in<N, INV>(buf, spec + base, es, colok, tid);
-    __syncthreads();
-    const int c = tid % TK, t = tid / TK;
-    fft_stages<N, T, 0, 1>(buf + c, TK, t, t < T, tw);
-    tile_out<N, INV>(buf, spec + base, es, colok, tid);
+    if (axis == 1) { base = (long long)other * ny * sh + kx; es = sh; }
+    else { base = (long long)other * sh + kx; es = (long long)sh * ny; }
+    const gptr<double2> line = (gptr<double2>)D.spec + (active ? base : 0);
+    constexpr int R0 = fft_radix<N, false>(0), NB = N / R0, MB = fft_per_thread<N, T, R0>();
+    double2 v[MB][R0];
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+        const int j = t + m * T < NB ? t + m * T : 0;
+#pragma unroll
+        for (int r = 0; r < R0; ++r) v[m][r] = gload2(line + (j + r * NB) * es);
+    }
+    if (INV) {
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int r = 0; r < R0; ++r) v[m][r] = cconj(v[m][r]);
+    }
+    fft_from<N, T, false, 0, 1, true>(v, buf[sub] + c, TK, t, active, tw,
+                                      [&](int k, double2 x, int, int) { gstore2(line + k * es, INV ? cconj(x) : x); });
 }
 
 // ---------------------------------------------------------------------------------------------
-// periodic: transform along z, divide by the Laplacian eigenvalue, transform back (in place)
+// periodic: transform along z, divide by the Laplacian eigenvalue, transform back (in place).  The way
+// back takes the radices in reverse order and so starts on the results where they are.
 // ---------------------------------------------------------------------------------------------
 template <int N>
-__global__ __launch_bounds__(NT) void k_solve_periodic(Batch B)
+__global__ __launch_bounds__(strided_block<N>()) void k_solve_periodic(Batch B)
 {
-    constexpr int T = strided_threads<N>();
-    __shared__ double2 buf[N * TK];
+    constexpr int T = strided_threads<N>(), NTL = strided_tiles<N>();
+    __shared__ double2 buf[NTL][N * TK];
     __shared__ double2 tw[N];
-    __shared__ double ez[N];        // Laplacian eigenvalues along z and of the block's kx columns
-    __shared__ double ex[TK];
+    __shared__ double ez[N];        // Laplacian eigenvalues along z
     const Desc& D = *B.d[blockIdx.y];
     const int tid = threadIdx.x;
-    const gptr<const double> eigx = (gptr<const double>)D.eigx;
-    const gptr<const double> eigz = (gptr<const double>)D.eigz;
-    for (int n = tid; n < N; n += NT) {
+    for (int n = tid; n < N; n += strided_block<N>()) {
         tw[n] = gload2((gptr<const double2>)D.twz + n);
-        ez[n] = eigz[n];
+        ez[n] = ((gptr<const double>)D.eigz)[n];
     }
-    const gptr<double2> spec = (gptr<double2>)D.spec;
     const int nh = D.nh, sh = D.sh, ny = D.ny;
     const int ntk = (nh + TK - 1) / TK;
-    const int tile = blockIdx.x % ntk, ky = blockIdx.x / ntk;
-    const int kx0 = tile * TK;
-    if (tid < TK) ex[tid] = kx0 + tid < nh ? eigx[kx0 + tid] : 0.0;
-    const long long base = (long long)ky * sh + kx0, es = (long long)sh * ny;
-    const bool colok = kx0 + tid % TK < nh;
-    tile_in<N, false>(buf, spec + base, es, colok, tid);
-    __syncthreads();
-    const int c = tid % TK, t = tid / TK;
-    fft_stages<N, T, 0, 1>(buf + c, TK, t, t < T, tw);
+    const int c = tid % TK, t = (tid / TK) % T, sub = tid / (TK * T);
+    const int id = blockIdx.x * NTL + sub;
+    const int kx = (id % ntk) * TK + c, ky = id / ntk;
+    const bool active = kx < nh && ky < ny;
+    const long long es = (long long)sh * ny;
+    const gptr<double2> line = (gptr<double2>)D.spec + (active ? (long long)ky * sh + kx : 0);
+    const double exy = active ? ((gptr<const double>)D.eigx)[kx] + ((gptr<const double>)D.eigy)[ky] : 1.0;
     const double scale = 1.0 / ((double)D.nx * ny * N);
-    const double ey = ((gptr<const double>)D.eigy)[ky];
-    for (int e = tid; e < N * TK; e += NT) {
-        const int kz = e / TK, cc = e - kz * TK;
-        const int kx = kx0 + cc;
-        double2 x = buf[e];
-        if (kx < nh) {
-            const double den = ex[cc] + ey + ez[kz];
-            const double f = (kx == 0 && ky == 0 && kz == 0) ? 0.0 : scale / den;
-            x = cscale(x, f);
-        }
-        buf[e] = cconj(x);        // inverse transform by conjugation
+    constexpr int NS = make_plan(N).nst;
+    constexpr int R0 = fft_radix<N, false>(0), NB = N / R0, MB = fft_per_thread<N, T, R0>();
+    constexpr int RL = fft_radix<N, false>(NS - 1), ML = fft_per_thread<N, T, RL>();
+    double2 v[MB][R0];
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+        const int j = t + m * T < NB ? t + m * T : 0;
+#pragma unroll
+        for (int r = 0; r < R0; ++r) v[m][r] = gload2(line + (j + r * NB) * es);
     }
-    __syncthreads();
-    fft_stages<N, T, 0, 1>(buf + c, TK, t, t < T, tw);
-    tile_out<N, true>(buf, spec + base, es, colok, tid);
+    double2 z[ML][RL];
+    fft_from<N, T, false, 0, 1, true>(v, buf[sub] + c, TK, t, active, tw, [&](int, double2 x, int m, int r) { z[m][r] = x; });
+    if constexpr (NS == 1) __syncthreads();      // ez is there (longer lines have passed a barrier)
+#pragma unroll
+    for (int m = 0; m < ML; ++m)
+#pragma unroll
+        for (int r = 0; r < RL; ++r) {
+            const int kz = (t + m * T < N / RL ? t + m * T : 0) + r * (N / RL);
+            const double f = (kx == 0 && ky == 0 && kz == 0) ? 0.0 : scale / (exy + ez[kz]);
+            z[m][r] = cconj(cscale(z[m][r], f));        // inverse transform by conjugation
+        }
+    fft_from<N, T, true, 0, 1, false>(z, buf[sub] + c, TK, t, active, tw,
+                                      [&](int k, double2 x, int, int) { gstore2(line + k * es, cconj(x)); });
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -612,54 +618,40 @@ __global__ __launch_bounds__(NT) void k_ifftx(Batch B)
     const int npairs = (nlines + 1) >> 1;
     const int pair0 = blockIdx.x * LP;
     const int sh = D.sh;
-    // Hermitian extension of two half spectra into one complex line; loads of eight elements are
-    // issued before their LDS stores
-    constexpr int M = (LP * N + NT - 1) / NT, G = M < 8 ? M : 8;
+    // Hermitian extension of two half spectra into one complex line a + i b, at the inputs of the
+    // thread's first butterflies
+    const int lp = tid / T, t = tid - (tid / T) * T;
+    const int pair = pair0 + lp;
+    const bool active = lp < LP && pair < npairs;
+    const int la = active ? 2 * pair : 0;
+    const bool two = active && la + 1 < nlines;
+    const gptr<const double2> sa = spec + (long long)la * sh, sb = spec + (long long)(two ? la + 1 : la) * sh;
+    constexpr int R0 = fft_radix<N, false>(0), NB = N / R0, MB = fft_per_thread<N, T, R0>();
+    double2 v[MB][R0];
 #pragma unroll
-    for (int g0 = 0; g0 < M; g0 += G) {
-        double2 av[G], bv[G];
+    for (int m = 0; m < MB; ++m) {
+        const int j = t + m * T < NB ? t + m * T : 0;
+        double2 av[R0], bv[R0];
 #pragma unroll
-        for (int m = 0; m < G; ++m) {
-            const int e = tid + (g0 + m) * NT;
-            const int ee = e < LP * N ? e : 0;
-            const int lp = ee / N, n = ee - lp * N;
-            const int pair = pair0 + lp;
-            const int la = pair < npairs ? 2 * pair : 0;
-            const int lb = (pair < npairs && la + 1 < nlines) ? la + 1 : la;
-            const int k = n <= N / 2 ? n : N - n;
-            av[m] = gload2(spec + (long long)la * sh + k);
-            bv[m] = gload2(spec + (long long)lb * sh + k);
+        for (int r = 0; r < R0; ++r) {
+            const int n = j + r * NB, k = n <= N / 2 ? n : N - n;
+            av[r] = gload2(sa + k);
+            bv[r] = gload2(sb + k);
         }
 #pragma unroll
-        for (int m = 0; m < G; ++m) {
-            const int e = tid + (g0 + m) * NT;
-            if (e >= LP * N) continue;
-            const int lp = e / N, n = e - lp * N;
-            const int pair = pair0 + lp;
-            double2 Z = make_double2(0.0, 0.0);
-            if (pair < npairs) {
-                double2 a = av[m];
-                double2 b = (2 * pair + 1 < nlines) ? bv[m] : make_double2(0.0, 0.0);
-                if (n > N / 2) { a = cconj(a); b = cconj(b); }
-                Z = make_double2(a.x - b.y, a.y + b.x);   // a + i b
-            }
-            buf[e] = cconj(Z);
+        for (int r = 0; r < R0; ++r) {
+            double2 a = av[r], b = two ? bv[r] : make_double2(0.0, 0.0);
+            if (j + r * NB > N / 2) { a = cconj(a); b = cconj(b); }
+            v[m][r] = make_double2(a.x - b.y, -(a.y + b.x));        // conjugated: inverse transform
         }
     }
-    __syncthreads();
-    const int lp = tid / T, t = tid - (tid / T) * T;
-    fft_stages<N, T, 0, 1>(buf + lp * N, 1, t, lp < LP, tw);
     // walls: zero-mean gauge (the mean of the Neumann solution, from the tridiagonal solve)
     const double pm = D.walls ? ((gptr<const double>)D.gauge)[0] : 0.0;
-    for (int e = tid; e < LP * N; e += NT) {
-        const int l2 = e / N, n = e - l2 * N;
-        const int pair = pair0 + l2;
-        if (pair >= npairs) continue;
-        const double2 z = cconj(buf[e]);
-        const int la = 2 * pair;
-        p[(long long)la * N + n] = z.x - pm;
-        if (la + 1 < nlines) p[(long long)(la + 1) * N + n] = z.y - pm;
-    }
+    const gptr<double> pa = p + (long long)la * N;
+    fft_from<N, T, false, 0, 1, true>(v, buf + (lp < LP ? lp : 0) * N, 1, t, active, tw, [&](int n, double2 x, int, int) {
+        pa[n] = x.x - pm;
+        if (two) pa[N + n] = -x.y - pm;
+    });
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -824,11 +816,11 @@ hipError_t launch_fft_strided(const Batch& b, int nx, int ny, int nz, int axis, 
     const int ntk = (nh + TK - 1) / TK;
     const int n = axis == 1 ? ny : nz;
     const int other = axis == 1 ? nz : ny;
-    dim3 grid(ntk * other, b.count);
 #define CALL(N)                                                                                  \
     {                                                                                            \
-        if (inverse) hipLaunchKernelGGL((k_fft_strided<N, true>), grid, dim3(NT), 0, s, b, axis); \
-        else hipLaunchKernelGGL((k_fft_strided<N, false>), grid, dim3(NT), 0, s, b, axis);       \
+        dim3 grid((ntk * other + strided_tiles<N>() - 1) / strided_tiles<N>(), b.count);         \
+        if (inverse) hipLaunchKernelGGL((k_fft_strided<N, true>), grid, dim3(strided_block<N>()), 0, s, b, axis); \
+        else hipLaunchKernelGGL((k_fft_strided<N, false>), grid, dim3(strided_block<N>()), 0, s, b, axis); \
     }
     EVP_FFT_SWITCH(n, CALL)
 #undef CALL
@@ -839,8 +831,11 @@ hipError_t launch_solve_periodic(const Batch& b, int nx, int ny, int nz, hipStre
 {
     const int nh = nx / 2 + 1;
     const int ntk = (nh + TK - 1) / TK;
-    dim3 grid(ntk * ny, b.count);
-#define CALL(N) hipLaunchKernelGGL(k_solve_periodic<N>, grid, dim3(NT), 0, s, b);
+#define CALL(N)                                                                                  \
+    {                                                                                            \
+        dim3 grid((ntk * ny + strided_tiles<N>() - 1) / strided_tiles<N>(), b.count);            \
+        hipLaunchKernelGGL(k_solve_periodic<N>, grid, dim3(strided_block<N>()), 0, s, b);        \
+    }
     EVP_FFT_SWITCH(nz, CALL)
 #undef CALL
     return hipGetLastError();

@@ -35,3 +35,21 @@ def test_segments_of_the_wall_solve(ny):
     G.project()
     assert_close({"u": ru, "v": rv, "w": rw, "p": rp}, gpu_state(G, ("u", "v", "w", "p")),
                  1e-12 * max(1.0, (ny / 256) ** 2), f"ny={ny}")
+
+
+# Line transforms of one, two, three and four radices in each direction, and lengths so short that a
+# block takes several tiles and its last one fewer.  Tolerance as above.
+@pytest.mark.parametrize("shape", [(8, 10, 12), (10, 8, 8), (12, 30, 10), (20, 12, 24), (48, 8, 30), (160, 10, 8),
+                                   (10, 240, 12), (8, 12, 320), (12, 8, 512), (30, 384, 8), (480, 8, 10)])
+def test_line_lengths_of_the_transforms(shape):
+    nx, ny, nz = shape
+    wl = _wl(nx, ny, nz, False, "oldroyd_b")
+    u, v, w, B = inputs.random_state(wl.shape, 6, walls=False)
+    s = oracle_solver(wl)
+    s.write_fields(u, v, w, B)
+    ru, rv, rw, rp = oracle.project(s.g, s.u, s.v, s.w, 1.0, s.r.rho)
+    G = gpu_grid(wl)
+    G.write_fields(*to_dev(u, v, w, B))
+    G.project()
+    assert_close({"u": ru, "v": rv, "w": rw, "p": rp}, gpu_state(G, ("u", "v", "w", "p")),
+                 1e-12 * max(1.0, (max(shape) / 256) ** 2), f"{shape}")
