@@ -41,7 +41,7 @@ STEP_BYTES = {k: v + 32 + 48 + 72 for k, v in PRED_BYTES.items()}
 STRESS_DIV_BYTES = {"fp64": 6 * 8 + 48, "mixed": 6 * 4 + 48}
 
 PRED_SOURCES = [os.path.join(HERE, "paper_1803_09563_amd", "csrc", f)
-                for f in ("k_predictor_zm.hip", "weno.h")]
+                for f in ("predictor_async.h", "weno.h")]
 # rocprofv3 summaries of the predictor on the headline workload: HBM bytes per launch
 # (FETCH_SIZE / WRITE_SIZE) and SQ counters, each tagged with the kernel sources' hash
 TRAFFIC_FILE = os.path.join(HERE, "profiles", "predictor_channel512_hbm_traffic.txt")

@@ -183,8 +183,7 @@ int evp_create_grid(int nx, int ny, int nz, double lx, double ly, double lz, int
  * stream's).  One such grid per device at a time: while it exists another call on that device
  * returns EVP_ERR_STATE; evp_destroy_grid waits for its stream and frees the slot.  The state is
  * cleared on creation (u = 0, B = I, p = 0), whatever an earlier grid left there.  All other calls
- * work on it as on any grid; it calls no hipMalloc/hipFree, and a channel grid in EVP_MIXED runs
- * the predictor's wall rows on its own stream (no side stream is created).  Work that other
+ * work on it as on any grid; it calls no hipMalloc/hipFree.  Work that other
  * code enqueues on that device's static workspace would race with it; only this entry point uses
  * it.  Enqueues a fill kernel and table uploads, and waits for the stream. */
 int evp_create_grid_static(int nx, int ny, int nz, double lx, double ly, double lz, int bc_y,

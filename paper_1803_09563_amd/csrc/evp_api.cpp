@@ -151,15 +151,25 @@ struct evp_grid {
     std::vector<hipEvent_t> free_events;
     long long prof_launches[EVP_K_COUNT];
     double prof_ms[EVP_K_COUNT];
-    evp::Side side;               // channel grids: second stream for the wall rows of the predictor
-    bool side_ready;
     int static_dev;               // device whose static workspace holds this grid; -1: caller's
 };
 
 namespace {
 
+template <typename T> void stage_constants(evp::StageConst<T>& k, const Desc& h)
+{
+    k.idx = (T)h.idx; k.idy = (T)h.idy; k.idz = (T)h.idz;
+    k.qx = (T)(0.25 * h.idx); k.qy = (T)(0.25 * h.idy); k.qz = (T)(0.25 * h.idz);
+    k.idx2 = (T)(h.idx * h.idx); k.idy2 = (T)(h.idy * h.idy); k.idz2 = (T)(h.idz * h.idz);
+    k.e2x = (T)(1e-6 * h.dx * h.dx); k.e2y = (T)(1e-6 * h.dy * h.dy); k.e2z = (T)(1e-6 * h.dz * h.dz);
+    k.G = (T)h.G; k.L2 = (T)h.L2; k.a_fene = (T)h.a_fene; k.inv_lam = (T)h.inv_lam; k.tau_y = (T)h.tau_y;
+    k.mu_s = (T)h.mu_s; k.inv_rho = (T)h.inv_rho; k.kappa = (T)h.kappa;
+}
+
 int upload_desc(evp_grid* g)
 {
+    stage_constants(g->h.kd, g->h);
+    stage_constants(g->h.kf, g->h);
     hipError_t e = hipMemcpyAsync(g->d, &g->h, sizeof(Desc), hipMemcpyHostToDevice, g->stream);
     if (e != hipSuccess) return hip_fail(e, "descriptor upload");
     e = hipStreamSynchronize(g->stream);
@@ -336,27 +346,6 @@ constexpr double kRkXi[3] = {0.0, -17.0 / 60.0, -5.0 / 12.0};
 // The predictor is specialised per constitutive model and advection scheme: one launch per
 // (model, scheme) pair present in the batch, so a grid's arithmetic is the same alone and in any
 // batch.
-// the side stream of a channel grid in the mixed form (the only one that runs the predictor's
-// wall rows beside its interior), created on first use at default priority; nullptr otherwise or
-// if it cannot be created, in which case the wall rows run after the interior on the main stream
-const evp::Side* side_of(evp_grid* g)
-{
-    if (g->bc != EVP_WALLS || g->precision != EVP_MIXED || g->static_dev >= 0) return nullptr;
-    if (!g->side_ready) {
-        evp::Side sd{nullptr, nullptr, nullptr};
-        if (hipStreamCreateWithFlags(&sd.s, hipStreamNonBlocking) != hipSuccess) return nullptr;
-        if (hipEventCreateWithFlags(&sd.fork, hipEventDisableTiming) != hipSuccess ||
-            hipEventCreateWithFlags(&sd.join, hipEventDisableTiming) != hipSuccess) {
-            if (sd.fork) (void)hipEventDestroy(sd.fork);
-            (void)hipStreamDestroy(sd.s);
-            return nullptr;
-        }
-        g->side = sd;
-        g->side_ready = true;
-    }
-    return &g->side;
-}
-
 int predictor_by_model(evp_grid* const* gs, const Batch& b, bool freeze, bool rk3, bool two_phase = false)
 {
     evp_grid* g0 = gs[0];
@@ -374,9 +363,15 @@ int predictor_by_model(evp_grid* const* gs, const Batch& b, bool freeze, bool rk
             }
         if (bm.count == 0) continue;
         r = timed(g0, EVP_K_PREDICTOR, [&] {
-            return evp::launch_predictor_zm(bm, g0->precision, g0->nx, g0->ny, g0->nz, freeze,
-                                            g0->stream, g0->bc == EVP_WALLS, model, rk3,
-                                            adv == EVP_HOUC5, two_phase, side_of(g0));
+            const bool houc = adv == EVP_HOUC5;
+            if (two_phase) {
+                // FP64 and Adams-Bashforth only (evp_set_two_phase, evp_step_rk3 see to it)
+                if (g0->precision != EVP_FP64 || rk3) return hipErrorInvalidValue;
+                return evp::launch_stress_two_phase(bm, g0->nx, g0->ny, g0->nz, g0->stream, g0->bc == EVP_WALLS, model, houc);
+            }
+            if (g0->precision == EVP_MIXED)
+                return evp::launch_predictor_mixed(bm, g0->nx, g0->ny, g0->nz, freeze, g0->stream, model, rk3, houc);
+            return evp::launch_predictor_fp64(bm, g0->nx, g0->ny, g0->nz, freeze, g0->stream, model, rk3, houc);
         });
     }
     return r;
@@ -630,9 +625,6 @@ int create_in(int nx, int ny, int nz, double lx, double ly, double lz, int bc_y,
     h.ps = L.ps;
     h.dx = lx / nx; h.dy = ly / ny; h.dz = lz / nz;
     h.idx = 1.0 / h.dx; h.idy = 1.0 / h.dy; h.idz = 1.0 / h.dz;
-    h.qx = 0.25 * h.idx; h.qy = 0.25 * h.idy; h.qz = 0.25 * h.idz;
-    h.idx2 = h.idx * h.idx; h.idy2 = h.idy * h.idy; h.idz2 = h.idz * h.idz;
-    h.e2x = 1e-6 * h.dx * h.dx; h.e2y = 1e-6 * h.dy * h.dy; h.e2z = 1e-6 * h.dz * h.dz;
     h.y0 = bc_y == EVP_WALLS ? -0.5 * ly : 0.0;
     h.rho = 1.0; h.inv_rho = 1.0; h.lam = 1.0; h.inv_lam = 1.0; h.L2 = 1e4;
     h.a_fene = h.L2 / (h.L2 - 3.0);
@@ -1130,12 +1122,6 @@ int evp_destroy_grid(evp_grid* g)
         (void)hipStreamSynchronize(g->stream);
         std::lock_guard<std::mutex> lock(g_static_mu);
         g_static_busy[g->static_dev] = false;
-    }
-    if (g->side_ready) {
-        (void)hipStreamSynchronize(g->side.s);
-        (void)hipEventDestroy(g->side.fork);
-        (void)hipEventDestroy(g->side.join);
-        (void)hipStreamDestroy(g->side.s);
     }
     delete g;
     return EVP_OK;

@@ -11,6 +11,11 @@ namespace evp {
 
 // Per-grid constants and pointers.  Lives at the start of the grid's workspace (device) and is
 // mirrored in the host-side grid; kernels read it through a uniform pointer (scalar loads).
+template <typename T> struct StageConst {
+    T idx, idy, idz, qx, qy, qz, idx2, idy2, idz2, e2x, e2y, e2z;   // 1/h, 1/(4h), 1/h^2 and 1e-6 h^2 per direction
+    T G, L2, a_fene, inv_lam, tau_y, mu_s, inv_rho, kappa;
+};
+
 struct Desc {
     int nx, ny, nz, nh;          // cells; nh = nx/2 + 1 complex values per x-spectrum line
     int walls;                   // EVP_WALLS in y?
@@ -31,7 +36,6 @@ struct Desc {
     long long ncell;             // nx*ny*nz
     long long ps;                // element stride between planes of B, RT, RU (256-byte padded)
     double dx, dy, dz, idx, idy, idz, y0;
-    double qx, qy, qz, idx2, idy2, idz2, e2x, e2y, e2z;   // 1/(4h), 1/h^2 and 1e-6 h^2 per direction
     double rho, inv_rho, mu_s, mu_p, lam, inv_lam, G, tau_y, L2, a_fene;
     double force_amp, force_ky;
     double u_bot, u_top, w_bot, w_top;
@@ -49,6 +53,8 @@ struct Desc {
                                  // every pivot of its modes below row ny-1 equals row ny-2's
     double* red;                 // reduction partials (health)
     double* gauge;               // walls: volume mean of p before the zero-mean gauge (one value)
+    StageConst<double> kd;       // the predictor's constants, in both types of its arithmetic
+    StageConst<float> kf;
 };
 
 // Argument block of every batched kernel (by value; < 1 KiB).
@@ -74,16 +80,13 @@ constexpr int ST_REINIT = 8;     // two-phase: this grid reinitialises its level
 constexpr int ST_FROM_U = 16;    // projection of the velocity itself: u takes the place of u*
 
 // Host-side launchers (one per kernel family); shape is common to the whole batch.
-// A second stream with a fork and a join event: work launched there runs beside the main
-// stream's and is joined back before the main stream goes on.
-struct Side { hipStream_t s; hipEvent_t fork, join; };
-hipError_t launch_predictor_zm(const Batch& b, int precision, int nx, int ny, int nz, bool freeze,
-                               hipStream_t s, bool walls, int model, bool rk3, bool houc,
-                               bool two_phase, const Side* side = nullptr);
-// the FP64 predictor with asynchronously staged planes (k_predictor_async.hip)
-hipError_t launch_predictor_async(const Batch& b, int nx, int ny, int nz, bool freeze, hipStream_t s,
+// the predictor with asynchronously staged planes (predictor_async.h)
+hipError_t launch_predictor_fp64(const Batch& b, int nx, int ny, int nz, bool freeze, hipStream_t s,
+                                 int model, bool rk3, bool houc);
+hipError_t launch_predictor_mixed(const Batch& b, int nx, int ny, int nz, bool freeze, hipStream_t s,
                                   int model, bool rk3, bool houc);
-// two-phase path (k_two_phase.hip)
+// two-phase path (k_two_phase_stress.hip, k_two_phase.hip)
+hipError_t launch_stress_two_phase(const Batch& b, int nx, int ny, int nz, hipStream_t s, bool walls, int model, bool houc);
 hipError_t launch_level_set_stage(const Batch& b, int nx, int ny, int nz, bool walls, bool reinit,
                                   int stage, hipStream_t s);
 hipError_t launch_reinit_sign(const Batch& b, int nx, int ny, int nz, hipStream_t s);

@@ -1,7 +1,6 @@
-// Predictor of the Adams-Bashforth step (Sec. 3.2.2, Eqs. (rt), (ab2tau), (ru), (ab2)) -- or of
-// one Runge-Kutta substep (Sec. 3.3.1) -- in the mixed form (FP32 stresses), and of the stress part
-// of the two-phase step (FP64), as a z-marching LDS-tiled kernel laid out for CDNA4 (the single-phase
-// FP64 predictor is k_predictor_async.hip):
+// Stress part of the two-phase step (Sec. 3.2, FP64, AB2; Eqs. (rt), (ab2tau)) as a z-marching
+// LDS-tiled kernel (the single-phase predictor is predictor_async.h, the two-phase momentum
+// k_two_phase.hip):
 //   * a block of 32 x 8 threads owns a 32 x 8 column of cells and marches along z over a chunk of
 //     planes, so every field is read from HBM about once;
 //   * the seven planes k-3..k+3 that the z-direction WENO needs for the thread's own cell live in
@@ -9,12 +8,9 @@
 //   * plane k of B - I, with the 3-cell cross halo of the x/y WENO stencils (ghost rows beyond a
 //     wall extrapolated at load time), sits in LDS;
 //   * three-plane rings in LDS hold the velocities and the stress components tau_xz, tau_yz,
-//     tau_zz of planes k-1, k, k+1 on the tile plus a 1-cell halo (momentum stencils and the
-//     velocity gradient);
+//     tau_zz of planes k-1, k, k+1 on the tile plus a 1-cell halo;
 //   * FENE-P stress factors G F and G (F - a) of plane k are staged once per cell.
 // Block ids are remapped so consecutive tiles land on the same XCD (shared L2 for halo reads).
-#include <cstdlib>
-
 #include "evp_internal.h"
 #include "weno.h"
 
@@ -42,8 +38,8 @@ __device__ __forceinline__ int modp(int i, int n)
 // (within one plane of one field).  BUF: as raw buffer instructions, whose descriptor (base, no
 // stride, 2^31 - 1 bytes; fourth word the raw-buffer format of CDNA, 32-bit data, no swizzle)
 // lives in scalar registers, so an access costs no vector arithmetic and no 64-bit address
-// registers (this lets the FP32 kernel run four waves per SIMD); otherwise as global
-// instructions on the base plus the zero-extended offset (measured faster for the FP64 kernel).
+// registers; otherwise as global instructions on the base plus the zero-extended offset (measured
+// faster for the periodic kernel).
 constexpr int kRawBufferWord3 = 0x00020000;
 // Cache policy of an access.  kKeep: data that neighbouring tiles read again as their halo
 // (B - I, u, v, w).  kStream: data that only this cell touches in this kernel (the history it
@@ -56,8 +52,7 @@ __device__ __forceinline__ T ldx(gptr<const T> base, unsigned boff)
 {
     if constexpr (BUF) {
         const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((EVP_GLOBAL void*)base, (short)0, 0x7fffffff, kRawBufferWord3);
-        if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, boff, 0, POL));
-        else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, boff, 0, POL));
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, boff, 0, POL));
     } else {
         const gptr<const T> a = (gptr<const T>)((gptr<const char>)base + boff);
         if constexpr (POL == kStream) return __builtin_nontemporal_load(a);
@@ -70,8 +65,7 @@ __device__ __forceinline__ void stx(gptr<T> base, unsigned boff, T v)
     if constexpr (BUF) {
         typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
         const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((EVP_GLOBAL void*)base, (short)0, 0x7fffffff, kRawBufferWord3);
-        if constexpr (sizeof(T) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, boff, 0, POL);
-        else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, boff, 0, POL);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, boff, 0, POL);
     } else {
         const gptr<T> a = (gptr<T>)((gptr<char>)base + boff);
         if constexpr (POL == kStream) __builtin_nontemporal_store(v, a);
@@ -118,22 +112,18 @@ __device__ __forceinline__ T weno_dir(T g0, T g1, T g2, T g3, T g4, T g5, T eps2
         return weno5u<T>(v1, v2, v3, v4, v5, eps2);
 }
 
-// RK3: the substep of Sec. 3.3.1 instead of AB2.  B^k = B^{k-1} + dt (zeta RT^{k-1} + xi RT^{k-2});
-// the momentum part leaves out the stress divergence at the new level (added by k_stress_div once
-// B^k is complete) and the pressure gradient (the projection then yields p^k itself), and keeps
-// the advection term as the history: u~ = u + dt [-zeta A^{k-1} - xi A^{k-2}
-// + (2 alpha (mu_s lap u + f) + alpha div tau^{k-1}) / rho].
 // HOUC: fifth-order upstream-central advection instead of WENO5 (a separate instantiation, so
 // the WENO kernel's register allocation is not shared with the other scheme).
-// TWOPH: two-phase mode (Sec. 3.2, FP64, AB2): lambda and G = mu_p/lambda of the cell come from
-// the mixture at phi^{n+1}; only the stress is advanced (the momentum has its own kernel).
+// lambda and G = mu_p/lambda of the cell come from the mixture at phi^{n+1}; only the stress is
+// advanced (the momentum has its own kernel).
 // The block's work: tile `bid` of the tile rows `rows`, z-chunks of kc planes.
-template <typename T, bool WALLS, int MODEL, bool RK3, bool HOUC, bool TWOPH>
-__device__ __forceinline__ void pred_block(Smem<T>& S, const Batch& B, int freeze, int kc, Rows rows, int bid)
+template <bool WALLS, int MODEL, bool HOUC>
+__device__ __forceinline__ void stress_block(Smem<double>& S, const Batch& B, int kc, Rows rows, int bid)
 {
-    // buffer-instruction accesses in the FP32 kernels and the FP64 wall kernel (which then keeps
-    // its ghost-row state in registers without spilling)
-    constexpr bool BUF = sizeof(T) == 4 || WALLS;
+    using T = double;
+    // buffer-instruction accesses in the wall kernel (which then keeps its ghost-row state in
+    // registers with less spilling)
+    constexpr bool BUF = WALLS;
     const int b = blockIdx.y;
     const Desc& D = *B.d[b];
     const int nx = D.nx, ny = D.ny, nz = D.nz;
@@ -157,23 +147,19 @@ __device__ __forceinline__ void pred_block(Smem<T>& S, const Batch& B, int freez
     const gptr<const T> __restrict__ Bin = (gptr<const T>)D.Bt[st & 1];
     const gptr<T> __restrict__ Bout = (gptr<T>)D.Bt[(st & 1) ^ 1];
     const gptr<T> __restrict__ RT = (gptr<T>)D.RT;
-    const gptr<T> __restrict__ RU = (gptr<T>)D.RU;
     const bool euler = (st & ST_EULER) != 0;
     const T dt = (T)B.dt[b];
-    // history weights: AB2 (3/2, -1/2; Euler start 1, 0) or the substep's (zeta, xi)
-    const T c1 = RK3 ? (T)B.rk[0] : (euler ? (T)1 : (T)1.5);
-    const T c2 = euler ? (T)0 : (RK3 ? (T)B.rk[1] : (T)-0.5);
+    // history weights: AB2 (3/2, -1/2; Euler start 1, 0)
+    const T c1 = euler ? (T)1 : (T)1.5;
+    const T c2 = euler ? (T)0 : (T)-0.5;
     constexpr bool fene = MODEL == EVP_FENE_P, sara = MODEL == EVP_SARAMITO, neo = MODEL == EVP_NEO_HOOKEAN;
     const T kap = (T)D.kappa;
-    const T G = (T)D.G, L2 = (T)D.L2, afene = (T)D.a_fene, il = (T)D.inv_lam, tyld = (T)D.tau_y;
+    const T G = (T)D.G, L2 = (T)D.L2, afene = (T)D.a_fene, tyld = (T)D.tau_y;
     const T idx = (T)D.idx, idy = (T)D.idy, idz = (T)D.idz;
     const T e2x = (T)(1e-6 * D.dx * D.dx), e2y = (T)(1e-6 * D.dy * D.dy), e2z = (T)(1e-6 * D.dz * D.dz);
     const gptr<const double> __restrict__ gu = (gptr<const double>)D.u;
     const gptr<const double> __restrict__ gv = (gptr<const double>)D.v;
     const gptr<const double> __restrict__ gw = (gptr<const double>)D.w;
-    const gptr<double> __restrict__ gus = (gptr<double>)D.us;
-    const gptr<double> __restrict__ gvs = (gptr<double>)D.vs;
-    const gptr<double> __restrict__ gws = (gptr<double>)D.ws;
 
     // ---- staging descriptors, computed once: the per-plane offsets do not depend on k ----
     // Interior slots (the block's own cells) are filled from the thread's register window; only
@@ -319,11 +305,6 @@ __device__ __forceinline__ void pred_block(Smem<T>& S, const Batch& B, int freez
         if (ownk) { (&S.gf[0][0])[own_x] = ogf; (&S.ga[0][0])[own_x] = oga; }
     };
 
-    // forcing on this thread's x-face row
-    T fx = (T)0;
-    if (D.force_kind == EVP_FORCE_CONST_X) fx = (T)D.force_amp;
-    else if (D.force_kind == EVP_FORCE_SIN_X_OF_Y) fx = (T)(D.force_amp * sin(D.force_ky * (D.y0 + (jc + 0.5) * D.dy)));
-
     // prologue: register window planes k0-3..k0+2, rings for planes k0-1 and k0
     T win[7][6];
 #pragma unroll
@@ -335,10 +316,7 @@ __device__ __forceinline__ void pred_block(Smem<T>& S, const Batch& B, int freez
     load_box(modp(k0 - 1, nz), win[2], (k0 + 2) % 3, 0, nullptr);
     load_box(k0, win[3], (k0 + 3) % 3, 0, nullptr);
 
-    const T ms = (T)D.mu_s, irho = (T)D.inv_rho;
-    const T idx2 = idx * idx, idy2 = idy * idy, idz2 = idz * idz;
     const T h = (T)0.5, qt = (T)0.25;
-    const bool vwall = WALLS && j == ny - 1;
 
     for (int k = k0; k < k1; ++k) {
         const int kp = modp(k + 1, nz);
@@ -375,13 +353,9 @@ __device__ __forceinline__ void pred_block(Smem<T>& S, const Batch& B, int freez
 
             // Table 1 closure of this cell
             const T* bt = win[3];
-            T Gc = G, ilc = il;
-            if constexpr (TWOPH) {
-                const double hh = heaviside(((gptr<const double>)D.phi)[q], D.eps_if);
-                const double lam = D.lam1 * hh + D.lam2 * (1.0 - hh), mup = D.mup1 * hh + D.mup2 * (1.0 - hh);
-                Gc = (T)(mup / lam);
-                ilc = (T)(1.0 / lam);
-            }
+            const double hh = heaviside(((gptr<const double>)D.phi)[q], D.eps_if);
+            const double lam = D.lam1 * hh + D.lam2 * (1.0 - hh), mup = D.mup1 * hh + D.mup2 * (1.0 - hh);
+            const T Gc = mup / lam, ilc = 1.0 / lam;
             T F = (T)1, a = (T)1;
             if (fene) {
                 F = L2 / (L2 - (bt[0] + bt[3] + bt[5] + (T)3));
@@ -412,33 +386,21 @@ __device__ __forceinline__ void pred_block(Smem<T>& S, const Batch& B, int freez
             const int cm[3][3] = {{0, 1, 2}, {1, 3, 4}, {2, 4, 5}};
             T rtv[6];
             {
-                // FP64: x and y stencils read from LDS in upwind order: element m of the x stencil
+                // x and y stencils read from LDS in upwind order: element m of the x stencil
                 // is column c + sx (m - 3), of the y stencil row r + sy (m - 3), with s = +1 for a
                 // non-negative velocity and -1 otherwise; the sign of the derivative then comes
                 // with |velocity| in the advection term (no selects; bitwise the same numbers).
-                // FP32 keeps the selects: the per-thread LDS addresses cost it registers at four
-                // waves per SIMD.
-                constexpr bool MIRROR = sizeof(T) == 8;
                 const int sx = uc >= (T)0 ? 1 : -1, sy = vc >= (T)0 ? RW : -RW;
                 const T* const bx = &S.B[0][r][c];
                 const T auc = uc >= (T)0 ? uc : -uc, avc = vc >= (T)0 ? vc : -vc;
 #pragma unroll
                 for (int cc = 0; cc < 6; ++cc) {
-                    T gx, gy;
-                    if constexpr (MIRROR) {
-                        const T* const pc = bx + cc * (RH * RW);
-                        gx = weno_dir<T, HOUC>(pc[-3 * sx], pc[-2 * sx], pc[-sx], pc[0], pc[sx], pc[2 * sx], e2x);
-                        gy = weno_dir<T, HOUC>(pc[-3 * sy], pc[-2 * sy], pc[-sy], pc[0], pc[sy], pc[2 * sy], e2y);
-                    } else {
-                        gx = weno_up<T, HOUC>(S.B[cc][r][c - 3], S.B[cc][r][c - 2], S.B[cc][r][c - 1], S.B[cc][r][c],
-                                              S.B[cc][r][c + 1], S.B[cc][r][c + 2], S.B[cc][r][c + 3], uc, e2x);
-                        gy = weno_up<T, HOUC>(S.B[cc][r - 3][c], S.B[cc][r - 2][c], S.B[cc][r - 1][c], S.B[cc][r][c],
-                                              S.B[cc][r + 1][c], S.B[cc][r + 2][c], S.B[cc][r + 3][c], vc, e2y);
-                    }
+                    const T* const pc = bx + cc * (RH * RW);
+                    const T gx = weno_dir<T, HOUC>(pc[-3 * sx], pc[-2 * sx], pc[-sx], pc[0], pc[sx], pc[2 * sx], e2x);
+                    const T gy = weno_dir<T, HOUC>(pc[-3 * sy], pc[-2 * sy], pc[-sy], pc[0], pc[sy], pc[2 * sy], e2y);
                     const T gz = weno_up<T, HOUC>(win[0][cc], win[1][cc], win[2][cc], win[3][cc], win[4][cc],
                                                   win[5][cc], win[6][cc], wc, e2z);
-                    const T adv = MIRROR ? auc * gx * idx + avc * gy * idy + wc * gz * idz
-                                         : uc * gx * idx + vc * gy * idy + wc * gz * idz;
+                    const T adv = auc * gx * idx + avc * gy * idy + wc * gz * idz;
                     const int p = pa[cc], rr = pb[cc];
                     T ucv = L[p][rr] + L[rr][p];
 #pragma unroll
@@ -461,120 +423,15 @@ __device__ __forceinline__ void pred_block(Smem<T>& S, const Batch& B, int freez
             // a load also waits for the stores issued before it
             // plane bases (uniform) and this cell's byte offsets within a plane
             const int kq = k * sxy;
-            const unsigned ob = (unsigned)(j * nx + i) * TS, o8 = (unsigned)(j * nx + i) * 8u;
+            const unsigned ob = (unsigned)(j * nx + i) * TS;
             T old[6];
 #pragma unroll
             for (int cc = 0; cc < 6; ++cc) old[cc] = euler ? (T)0 : ldx<BUF, T, kStream>(RT + (kq + cc * ps), ob);
-            double u0, v0, w0;
-            if constexpr (!WALLS && sizeof(T) == 8) {
-                // this cell's velocities are in the ring slot of plane k (in FP64 the loaded values
-                // themselves), so they need no second load
-                u0 = VU(s0, 0, 0); v0 = VV(s0, 0, 0); w0 = VW(s0, 0, 0);
-            } else {
-                u0 = ldx<BUF, double>(gu + kq, o8); v0 = ldx<BUF, double>(gv + kq, o8); w0 = ldx<BUF, double>(gw + kq, o8);
-            }
-            T ox = (T)0, oy = (T)0, oz = (T)0;
-            if (!euler && !freeze) {
-                ox = ldx<BUF, T, kStream>(RU + kq, ob); oy = ldx<BUF, T, kStream>(RU + (kq + ps), ob);
-                oz = ldx<BUF, T, kStream>(RU + (kq + 2 * ps), ob);
-            }
-            // the stress results are stored after the momentum part, so that the history loads
-            // above are in flight during it
-            auto store_stress = [&]() {
 #pragma unroll
-                for (int cc = 0; cc < 6; ++cc) {
-                    stx<BUF, T>(Bout + (kq + cc * ps), ob, bt[cc] + dt * (c1 * rtv[cc] + c2 * old[cc]));
-                    stx<BUF, T>(RT + (kq + cc * ps), ob, rtv[cc]);
-                }
-            };
-            if constexpr (!(sizeof(T) == 8 && !WALLS)) {
-                store_stress();
-                __asm__ volatile("" ::: "memory");
+            for (int cc = 0; cc < 6; ++cc) {
+                stx<BUF, T>(Bout + (kq + cc * ps), ob, bt[cc] + dt * (c1 * rtv[cc] + c2 * old[cc]));
+                stx<BUF, T>(RT + (kq + cc * ps), ob, rtv[cc]);
             }
-            if constexpr (TWOPH) {
-                // the two-phase momentum follows in k_momentum_two_phase
-            } else if (freeze) {
-                stx<BUF, double>(gus + kq, o8, u0); stx<BUF, double>(gvs + kq, o8, v0); stx<BUF, double>(gws + kq, o8, w0);
-                stx<BUF, T>(RU + kq, ob, (T)0); stx<BUF, T>(RU + (kq + ps), ob, (T)0); stx<BUF, T>(RU + (kq + 2 * ps), ob, (T)0);
-            } else {
-                // stresses of plane k from B - I and the staged factors
-#define TK(cc, di, dj) (fene ? (S.gf[rb + (dj)][cb + (di)] * S.B[cc][r + (dj)][c + (di)] + \
-                        (((cc) == 0 || (cc) == 3 || (cc) == 5) ? S.ga[rb + (dj)][cb + (di)] : (T)0)) \
-                        : G * S.B[cc][r + (dj)][c + (di)])
-#define TZ(s, zc, di, dj) S.Z[s][zc][rb + (dj)][cb + (di)]
-                // face terms; RK3 keeps the advection (history) apart from the rest (mx, my, mz)
-                const T cal = RK3 ? (T)B.rk[2] : (T)0;
-                T mx = (T)0, my = (T)0, mz = (T)0;
-                // x-face (i+1/2, j, k)
-                T rux;
-                {
-                    const T u0 = VU(s0, 0, 0), ue = VU(s0, 1, 0), uw = VU(s0, -1, 0);
-                    const T un = VU(s0, 0, 1), us = VU(s0, 0, -1), uf = VU(sp, 0, 0), ub = VU(sm, 0, 0);
-                    const T cR = h * (u0 + ue), cL = h * (uw + u0);
-                    const T vT = h * (VV(s0, 0, 0) + VV(s0, 1, 0)), vB = h * (VV(s0, 0, -1) + VV(s0, 1, -1));
-                    const T wF = h * (VW(s0, 0, 0) + VW(s0, 1, 0)), wB = h * (VW(sm, 0, 0) + VW(sm, 1, 0));
-                    const T adv = (cR * cR - cL * cL) * idx + (vT * h * (u0 + un) - vB * h * (us + u0)) * idy
-                                + (wF * h * (u0 + uf) - wB * h * (ub + u0)) * idz;
-                    const T lap = (ue - (T)2 * u0 + uw) * idx2 + (un - (T)2 * u0 + us) * idy2
-                                + (uf - (T)2 * u0 + ub) * idz2;
-                    const T dtau = (TK(0, 1, 0) - TK(0, 0, 0)) * idx
-                                 + qt * (TK(1, 0, 1) + TK(1, 1, 1) - TK(1, 0, -1) - TK(1, 1, -1)) * idy
-                                 + qt * (TZ(sp, 0, 0, 0) + TZ(sp, 0, 1, 0) - TZ(sm, 0, 0, 0) - TZ(sm, 0, 1, 0)) * idz;
-                    if constexpr (RK3) { rux = adv; mx = (T)2 * cal * (ms * lap + fx) + cal * dtau; }
-                    else rux = -adv + (ms * lap + dtau + fx) * irho;
-                }
-                // y-face (i, j+1/2, k)
-                T ruy = (T)0;
-                if (!vwall) {
-                    const T v0 = VV(s0, 0, 0), vn = VV(s0, 0, 1), vs = VV(s0, 0, -1);
-                    const T ve = VV(s0, 1, 0), vw = VV(s0, -1, 0), vf = VV(sp, 0, 0), vb = VV(sm, 0, 0);
-                    const T cT = h * (v0 + vn), cB = h * (vs + v0);
-                    const T uR = h * (VU(s0, 0, 0) + VU(s0, 0, 1)), uL = h * (VU(s0, -1, 0) + VU(s0, -1, 1));
-                    const T wF = h * (VW(s0, 0, 0) + VW(s0, 0, 1)), wB = h * (VW(sm, 0, 0) + VW(sm, 0, 1));
-                    const T adv = (uR * h * (v0 + ve) - uL * h * (vw + v0)) * idx + (cT * cT - cB * cB) * idy
-                                + (wF * h * (v0 + vf) - wB * h * (vb + v0)) * idz;
-                    const T lap = (ve - (T)2 * v0 + vw) * idx2 + (vn - (T)2 * v0 + vs) * idy2
-                                + (vf - (T)2 * v0 + vb) * idz2;
-                    const T dtau = qt * (TK(1, 1, 0) + TK(1, 1, 1) - TK(1, -1, 0) - TK(1, -1, 1)) * idx
-                                 + (TK(3, 0, 1) - TK(3, 0, 0)) * idy
-                                 + qt * (TZ(sp, 1, 0, 0) + TZ(sp, 1, 0, 1) - TZ(sm, 1, 0, 0) - TZ(sm, 1, 0, 1)) * idz;
-                    if constexpr (RK3) { ruy = adv; my = (T)2 * cal * (ms * lap) + cal * dtau; }
-                    else ruy = -adv + (ms * lap + dtau) * irho;
-                }
-                // z-face (i, j, k+1/2)
-                T ruz;
-                {
-                    const T w0 = VW(s0, 0, 0), wf = VW(sp, 0, 0), wb = VW(sm, 0, 0);
-                    const T we = VW(s0, 1, 0), ww = VW(s0, -1, 0), wn = VW(s0, 0, 1), wsv = VW(s0, 0, -1);
-                    const T cF = h * (w0 + wf), cB = h * (wb + w0);
-                    const T uR = h * (VU(s0, 0, 0) + VU(sp, 0, 0)), uL = h * (VU(s0, -1, 0) + VU(sp, -1, 0));
-                    const T vT = h * (VV(s0, 0, 0) + VV(sp, 0, 0)), vB = h * (VV(s0, 0, -1) + VV(sp, 0, -1));
-                    const T adv = (uR * h * (w0 + we) - uL * h * (ww + w0)) * idx
-                                + (vT * h * (w0 + wn) - vB * h * (wsv + w0)) * idy + (cF * cF - cB * cB) * idz;
-                    const T lap = (we - (T)2 * w0 + ww) * idx2 + (wn - (T)2 * w0 + wsv) * idy2
-                                + (wf - (T)2 * w0 + wb) * idz2;
-                    const T dtau = qt * (TZ(s0, 0, 1, 0) + TZ(sp, 0, 1, 0) - TZ(s0, 0, -1, 0) - TZ(sp, 0, -1, 0)) * idx
-                                 + qt * (TZ(s0, 1, 0, 1) + TZ(sp, 1, 0, 1) - TZ(s0, 1, 0, -1) - TZ(sp, 1, 0, -1)) * idy
-                                 + (TZ(sp, 2, 0, 0) - TZ(s0, 2, 0, 0)) * idz;
-                    if constexpr (RK3) { ruz = adv; mz = (T)2 * cal * (ms * lap) + cal * dtau; }
-                    else ruz = -adv + (ms * lap + dtau) * irho;
-                }
-#undef TK
-#undef TZ
-                if constexpr (RK3) {
-                    // the stress divergence at B^k and any solid penalisation follow in k_stress_div
-                    stx<BUF, double>(gus + kq, o8, u0 + (double)(dt * (mx * irho - c1 * rux - c2 * ox)));
-                    stx<BUF, double>(gvs + kq, o8, vwall ? 0.0 : v0 + (double)(dt * (my * irho - c1 * ruy - c2 * oy)));
-                    stx<BUF, double>(gws + kq, o8, w0 + (double)(dt * (mz * irho - c1 * ruz - c2 * oz)));
-                } else {
-                    // a solid, if any, is applied by k_penalise once u* is complete
-                    stx<BUF, double>(gus + kq, o8, u0 + (double)(dt * (c1 * rux + c2 * ox)));
-                    stx<BUF, double>(gvs + kq, o8, vwall ? 0.0 : v0 + (double)(dt * (c1 * ruy + c2 * oy)));
-                    stx<BUF, double>(gws + kq, o8, w0 + (double)(dt * (c1 * ruz + c2 * oz)));
-                }
-                stx<BUF, T>(RU + kq, ob, rux); stx<BUF, T>(RU + (kq + ps), ob, ruy); stx<BUF, T>(RU + (kq + 2 * ps), ob, ruz);
-            }
-            if constexpr (sizeof(T) == 8 && !WALLS) store_stress();
 #undef VU
 #undef VV
 #undef VW
@@ -587,37 +444,26 @@ __device__ __forceinline__ void pred_block(Smem<T>& S, const Batch& B, int freez
     }
 }
 
-template <typename T, bool WALLS, int MODEL, bool RK3, bool HOUC, bool TWOPH>
-__global__ __launch_bounds__(NTH, (sizeof(T) == 4 && !WALLS) ? 4 : 2) void k_pred_zm(Batch B, int freeze, int kc, Rows rows)
+template <bool WALLS, int MODEL, bool HOUC>
+__global__ __launch_bounds__(NTH, 2) void k_stress_two_phase(Batch B, int kc, Rows rows)
 {
-    __shared__ Smem<T> S;
-    pred_block<T, WALLS, MODEL, RK3, HOUC, TWOPH>(S, B, freeze, kc, rows, blockIdx.x);
+    __shared__ Smem<double> S;
+    stress_block<WALLS, MODEL, HOUC>(S, B, kc, rows, blockIdx.x);
 }
 
 }  // namespace
 
-// planes per block: `target` blocks per grid in total (EVP_PRED_BLOCKS overrides it), at least 4
-// planes per block.  Measured on one MI355X (the FP32 periodic kernel keeps four blocks per CU
-// resident): periodic grids run best with about one round of resident blocks (1024), channels with
-// about two (2048), whose shorter z-chunks leave a shorter last round
-int predictor_chunk_tiles(int tiles, int nz, int target)
+// planes per block: `target` blocks per grid in total, at least 4 planes per block (periodic grids: one
+// round of resident blocks; channels: shorter chunks, which leave a shorter last round)
+static int chunk_planes(int tiles, int nz, int target)
 {
-    static const int target_env = [] {
-        const char* e = std::getenv("EVP_PRED_BLOCKS");
-        return e ? std::atoi(e) : 0;
-    }();
-    if (target_env > 0) target = target_env;
     int nch = (target + tiles - 1) / tiles;
     nch = max(1, min(nch, nz / 4));
     return (nz + nch - 1) / nch;
 }
 
-
-hipError_t launch_predictor_zm(const Batch& b, int precision, int nx, int ny, int nz, bool freeze,
-                               hipStream_t s, bool walls, int model, bool rk3, bool houc,
-                               bool two_phase, const Side* side)
+hipError_t launch_stress_two_phase(const Batch& b, int nx, int ny, int nz, hipStream_t s, bool walls, int model, bool houc)
 {
-    if (precision == EVP_FP64 && !two_phase) return launch_predictor_async(b, nx, ny, nz, freeze, s, model, rk3, houc);
     const int ntx = (nx + TX - 1) / TX, nty = (ny + TY - 1) / TY;
     // Channel: tile rows whose whole stencil (B rows j0-3 .. j0+TY+2, velocity rows j0-1 ..
     // j0+TY) lies in rows 0 .. ny-3 never see a ghost row or the top wall face; they run the
@@ -625,7 +471,6 @@ hipError_t launch_predictor_zm(const Batch& b, int precision, int nx, int ny, in
     // rows next to the walls the wall instantiation.
     int in_lo = 1, in_hi = walls ? (ny - 3) / TY : 0;
     if (in_hi <= in_lo) in_lo = in_hi = 0;
-    const int fz = freeze ? 1 : 0;
     struct Part { bool w; Rows rows; };
     Part parts[2];
     int np = 0;
@@ -635,69 +480,26 @@ hipError_t launch_predictor_zm(const Batch& b, int precision, int nx, int ny, in
         if (in_hi > in_lo) parts[np++] = {true, {0, nty - (in_hi - in_lo), in_lo, in_hi - in_lo}};
         else parts[np++] = {true, {0, nty, 1 << 30, 0}};
     }
-    // In the mixed form the rows next to the walls run beside the interior on the side stream
-    // (measured faster for 256x128x128 and 512x256x256 channels: the FP32 wall and interior kernels
-    // differ in occupancy, so one grid would run both at the wall kernel's).  The two-phase mode
-    // launches the parts one after the other.
-    const bool fork = np == 2 && side != nullptr && precision == EVP_MIXED;
-    if (fork) {
-        hipError_t e = hipEventRecord(side->fork, s);
-        if (e == hipSuccess) e = hipStreamWaitEvent(side->s, side->fork, 0);
-        if (e != hipSuccess) return e;
-    }
     for (int ip = 0; ip < np; ++ip) {
-    const bool pw = parts[ip].w;
-    const Rows rows = parts[ip].rows;
-    const hipStream_t ls = (fork && pw) ? side->s : s;
-    const int kc = predictor_chunk_tiles(ntx * rows.count, nz, walls ? 2048 : (precision == EVP_MIXED ? 1024 : 512));
-    const int nblk = ntx * rows.count * ((nz + kc - 1) / kc);
-    dim3 grid(nblk, b.count);
-#define EVP_LAUNCH2(TT, WW, MM, RR)                                                                \
+        const Rows rows = parts[ip].rows;
+        const int kc = chunk_planes(ntx * rows.count, nz, walls ? 2048 : 512);
+        dim3 grid(ntx * rows.count * ((nz + kc - 1) / kc), b.count);
+#define EVP_LAUNCH(WW, MM)                                                                         \
     do {                                                                                           \
-        if (houc) hipLaunchKernelGGL((k_pred_zm<TT, WW, MM, RR, true, false>), grid, dim3(NTH), 0, ls, b, fz, kc, rows); \
-        else hipLaunchKernelGGL((k_pred_zm<TT, WW, MM, RR, false, false>), grid, dim3(NTH), 0, ls, b, fz, kc, rows); \
+        if (houc) hipLaunchKernelGGL((k_stress_two_phase<WW, MM, true>), grid, dim3(NTH), 0, s, b, kc, rows); \
+        else hipLaunchKernelGGL((k_stress_two_phase<WW, MM, false>), grid, dim3(NTH), 0, s, b, kc, rows);   \
     } while (0)
-#define EVP_LAUNCH_TP(WW, MM)                                                                      \
-    do {                                                                                           \
-        if (houc) hipLaunchKernelGGL((k_pred_zm<double, WW, MM, false, true, true>), grid, dim3(NTH), 0, ls, b, fz, kc, rows); \
-        else hipLaunchKernelGGL((k_pred_zm<double, WW, MM, false, false, true>), grid, dim3(NTH), 0, ls, b, fz, kc, rows); \
-    } while (0)
-#define EVP_LAUNCH(TT, WW, MM)                                                                     \
-    do {                                                                                           \
-        if (rk3) EVP_LAUNCH2(TT, WW, MM, true);                                                    \
-        else EVP_LAUNCH2(TT, WW, MM, false);                                                       \
-    } while (0)
-#define EVP_BY_MODEL(TT, WW)                                                                       \
+#define EVP_BY_MODEL(WW)                                                                           \
     switch (model) {                                                                               \
-    case EVP_FENE_P: EVP_LAUNCH(TT, WW, EVP_FENE_P); break;                                       \
-    case EVP_SARAMITO: EVP_LAUNCH(TT, WW, EVP_SARAMITO); break;                                   \
-    case EVP_NEO_HOOKEAN: EVP_LAUNCH(TT, WW, EVP_NEO_HOOKEAN); break;                             \
-    default: EVP_LAUNCH(TT, WW, EVP_OLDROYD_B); break;                                            \
+    case EVP_FENE_P: EVP_LAUNCH(WW, EVP_FENE_P); break;                                           \
+    case EVP_SARAMITO: EVP_LAUNCH(WW, EVP_SARAMITO); break;                                       \
+    case EVP_NEO_HOOKEAN: EVP_LAUNCH(WW, EVP_NEO_HOOKEAN); break;                                 \
+    default: EVP_LAUNCH(WW, EVP_OLDROYD_B); break;                                                \
     }
-    if (two_phase) {
-        if (precision != EVP_FP64 || rk3) return hipErrorInvalidValue;
-#define EVP_TP_BY_MODEL(WW)                                                                        \
-    switch (model) {                                                                               \
-    case EVP_FENE_P: EVP_LAUNCH_TP(WW, EVP_FENE_P); break;                                        \
-    case EVP_SARAMITO: EVP_LAUNCH_TP(WW, EVP_SARAMITO); break;                                    \
-    case EVP_NEO_HOOKEAN: EVP_LAUNCH_TP(WW, EVP_NEO_HOOKEAN); break;                              \
-    default: EVP_LAUNCH_TP(WW, EVP_OLDROYD_B); break;                                             \
-    }
-        if (pw) { EVP_TP_BY_MODEL(true) } else { EVP_TP_BY_MODEL(false) }
-#undef EVP_TP_BY_MODEL
-    } else {
-        if (pw) { EVP_BY_MODEL(float, true) } else { EVP_BY_MODEL(float, false) }
-    }
-    }
-    if (fork) {
-        hipError_t e = hipEventRecord(side->join, side->s);
-        if (e == hipSuccess) e = hipStreamWaitEvent(s, side->join, 0);
-        if (e != hipSuccess) return e;
-    }
+        if (parts[ip].w) { EVP_BY_MODEL(true) } else { EVP_BY_MODEL(false) }
 #undef EVP_BY_MODEL
 #undef EVP_LAUNCH
-#undef EVP_LAUNCH2
-#undef EVP_LAUNCH_TP
+    }
     return hipGetLastError();
 }
 

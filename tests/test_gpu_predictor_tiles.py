@@ -78,3 +78,47 @@ def test_batch_chunks_equal_single_bitwise(walls):
         sa, sc = gpu_state(a), gpu_state(c)
         for k in sa:
             assert np.array_equal(sa[k], sc[k]), k
+
+
+# The mixed form (FP32 stresses): widths that are and are not multiples of 4 (groups of 16 bytes or single
+# values), narrow and wide tiles, every wall-row remainder class.  Stored values are rounded to 6e-8 and
+# dt times right-hand sides of up to 10^2, themselves good to 1e-6, adds 1e-7: 5e-6 leaves a factor of 20.
+@pytest.mark.parametrize("model", ["saramito", "fene_p"])
+@pytest.mark.parametrize("shape,walls", [((8, 8, 8), False), ((10, 20, 10), False), ((30, 12, 8), False), ((40, 12, 8), False),
+                                         ((96, 96, 48), False), ((128, 64, 40), False), ((10, 9, 8), True), ((24, 8, 10), True),
+                                         ((24, 13, 10), True), ((48, 17, 10), True), ((128, 75, 64), True)])
+def test_mixed_tiles(shape, walls, model):
+    import paper_1803_09563_amd as evp
+    wl, fields = _stage(shape, model, walls)
+    s = oracle_solver(wl)
+    s.write_fields(*fields)
+    s.step(1e-3, 1, flags=oracle.Solver.STOP_AFTER_PREDICTOR)
+    G = gpu_grid(wl, precision=evp.MIXED)
+    G.write_fields(*to_dev(*fields))
+    G.step(1e-3, 1, flags=2)
+    assert_close(oracle_state(s), gpu_state(G, ("u", "v", "w", "B")), 5e-6, f"{shape} {model} mixed")
+
+
+# a grid's numbers do not depend on its tile and chunk: alone a 48^3 grid runs in narrow tiles, a batch
+# of 24 of them in wide ones
+@pytest.mark.parametrize("walls", [False, True])
+@pytest.mark.parametrize("adv", [0, 1])
+def test_mixed_batch_tiles_equal_single_bitwise(adv, walls):
+    import paper_1803_09563_amd as evp
+    singles, batched = [], []
+    for b in range(24):
+        wl, fields = _stage((48, 48, 48), ("saramito", "fene_p", "oldroyd_b", "oldroyd_b")[b % 4], walls, seed=200 + b)
+        wl.adv, wl.kappa = adv, 1e-3 * (b & 1)
+        if b % 4 == 3:
+            wl.model = evp.NEO_HOOKEAN
+        a, c = gpu_grid(wl, precision=evp.MIXED), gpu_grid(wl, precision=evp.MIXED)
+        for G in (a, c):
+            G.write_fields(*to_dev(*fields))
+        a.step(1e-3, 2)
+        singles.append(a)
+        batched.append(c)
+    evp.step_batch(batched, 1e-3, 2)
+    for a, c in zip(singles, batched):
+        sa, sc = gpu_state(a), gpu_state(c)
+        for k in sa:
+            assert np.array_equal(sa[k], sc[k]), k
