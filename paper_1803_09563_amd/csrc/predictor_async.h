@@ -449,14 +449,15 @@ __device__ __forceinline__ void march(SmemA<T, TX, TY, MODEL == EVP_FENE_P>& S, 
             for (int cc = 0; cc < 6; ++cc) bt[cc] = S.B[cur][cc][rB][cB];
             T F = (T)1, a = (T)1;
             if (fene) {
-                F = L2 / (L2 - (bt[0] + bt[3] + bt[5] + (T)3));
+                F = S.F[k & 1][rV][cV];
                 a = C.a_fene;
             } else if (sara) {
                 const T t3 = G * (bt[0] + bt[3] + bt[5]) * (T)(1.0 / 3.0);
                 const T dxx = G * bt[0] - t3, dyy = G * bt[3] - t3, dzz = G * bt[5] - t3;
                 const T txy = G * bt[1], txz = G * bt[2], tyz = G * bt[4];
-                const T nrm = sqrt((T)0.5 * (dxx * dxx + dyy * dyy + dzz * dzz) + txy * txy + txz * txz + tyz * tyz);
-                F = (tyld == (T)0) ? (T)1 : (nrm > tyld ? (T)1 - tyld / nrm : (T)0);
+                const T n2 = (T)0.5 * (dxx * dxx + dyy * dyy + dzz * dzz) + txy * txy + txz * txz + tyz * tyz;
+                // 1 - tau_y / |tau_d| above the yield stress
+                F = n2 > tyld * tyld ? (T)1 - tyld * fast_rsqrt(n2) : (tyld == (T)0 ? (T)1 : (T)0);
                 a = F;
             } else if (neo) {
                 F = (T)0;
