@@ -83,6 +83,7 @@ constexpr int ST_FROM_U = 16;    // projection of the velocity itself: u takes t
 // the predictor with asynchronously staged planes (predictor_async.h)
 hipError_t launch_predictor_fp64(const Batch& b, int nx, int ny, int nz, bool freeze, hipStream_t s,
                                  int model, bool rk3, bool houc);
+// model -1: grids of several models (not with rk3)
 hipError_t launch_predictor_mixed(const Batch& b, int nx, int ny, int nz, bool freeze, hipStream_t s,
                                   int model, bool rk3, bool houc);
 // two-phase path (k_two_phase_stress.hip, k_two_phase.hip)

@@ -712,6 +712,8 @@ __device__ __forceinline__ void march(SmemA<T, TX, TY, MODEL == EVP_FENE_P>& S, 
     if (valid) store_results(k1 - 1);
 }
 
+constexpr int kAnyModel = -1;      // several models in one launch
+
 // Waves per SIMD the registers are to allow.  Mixed form, wide tiles: three blocks fit a CU's LDS, and six
 // waves in 80 registers (a few spilled) beat four in 90 where a grid fills them (512x256x256 Saramito:
 // 1446 against 1580 us; 128^3: 105 against 107); FENE-P, with 20 spilled, gains nothing (256x128x128: 248
@@ -728,6 +730,27 @@ __global__ __launch_bounds__(2 * TX * TY, (min_waves<T, TX, MODEL>())) void k_pr
     // whole waves take either branch; both run the same sequence of barriers
     if (__builtin_amdgcn_readfirstlane((int)threadIdx.x / (TX * TY)) == 0) march<T, W, 0, TX, TY, MODEL, RK3, HOUC>(S, B, freeze, kc);
     else march<T, W, 1, TX, TY, MODEL, RK3, HOUC>(S, B, freeze, kc);
+}
+
+// Grids of several models in one launch (Adams-Bashforth): a block takes the march of its grid's model.
+template <typename T, int W, int TX, int TY, bool HOUC>
+__global__ __launch_bounds__(2 * TX * TY, (min_waves<T, TX, EVP_SARAMITO>())) void k_pred_async_models(Batch B, int freeze, int kc)
+{
+    __shared__ __align__(16) char mem[sizeof(SmemA<T, TX, TY, true>)];
+    const bool first = __builtin_amdgcn_readfirstlane((int)threadIdx.x / (TX * TY)) == 0;
+#define EVP_MARCH(MM)                                                                              \
+    do {                                                                                           \
+        auto& S = *(SmemA<T, TX, TY, (MM) == EVP_FENE_P>*)mem;                                     \
+        if (first) march<T, W, 0, TX, TY, MM, false, HOUC>(S, B, freeze, kc);                      \
+        else march<T, W, 1, TX, TY, MM, false, HOUC>(S, B, freeze, kc);                            \
+    } while (0)
+    switch (((const CDesc*)B.d[blockIdx.y])->model) {
+    case EVP_FENE_P: EVP_MARCH(EVP_FENE_P); break;
+    case EVP_SARAMITO: EVP_MARCH(EVP_SARAMITO); break;
+    case EVP_NEO_HOOKEAN: EVP_MARCH(EVP_NEO_HOOKEAN); break;
+    default: EVP_MARCH(EVP_OLDROYD_B); break;
+    }
+#undef EVP_MARCH
 }
 
 // Planes per block and its cost, for tiles of which `slots` fill the chip.  In units of one plane of
@@ -762,6 +785,13 @@ hipError_t launch_tile(const Batch& b, int nx, int ny, int nz, int kc, int fz, h
         else { if (houc) EVP_L(MM, false, true); else EVP_L(MM, false, false); }                   \
     } while (0)
     switch (model) {
+    case kAnyModel:
+        if constexpr (sizeof(T) == 4) {
+            if (rk3) return hipErrorInvalidValue;
+            if (houc) hipLaunchKernelGGL((k_pred_async_models<T, W, TX, TY, true>), grid, dim3(2 * TX * TY), 0, s, b, fz, kc);
+            else hipLaunchKernelGGL((k_pred_async_models<T, W, TX, TY, false>), grid, dim3(2 * TX * TY), 0, s, b, fz, kc);
+            break;
+        } else return hipErrorInvalidValue;
     case EVP_FENE_P:
         if constexpr (TX == 16 || sizeof(T) == 4) { EVP_M(EVP_FENE_P); break; }
         else return hipErrorInvalidValue;
