@@ -777,12 +777,14 @@ hipError_t launch_ifftx(const Batch& b, int nx, int ny, int nz, hipStream_t s)
 
 bool plane_transforms(int nx, int ny, int nz, int count)
 {
-    // one block per z plane and at most one per CU at 128^2: with fewer planes than the chip's 256
-    // CUs the separate line-transform passes are as fast (measured on one 128^3 grid); with at
-    // least that many, the fused passes save 2-11 % of the step (batches of 32^3 to 128^3 grids)
+    // One block per z plane.  Up to 64^2 a plane's block takes little longer than the blocks of the
+    // separate passes, and two launches fewer count: a step of one 32^3 grid 39 -> 28 us, 48^3 49 -> 41.5,
+    // 64^3 59 -> 56.  Above, one block per CU and as many planes as the chip has CUs are needed: one
+    // 96^3 grid 121 us separately and 132 fused, 128^3 237 and 254; with at least 256 planes the fused passes
+    // save 2-11 % of the step (batches of 96^3 and 128^3 grids)
     const bool size = nx == ny && (nx == 16 || nx == 24 || nx == 32 || nx == 48 || nx == 64 ||
                                    nx == 96 || nx == 128);
-    return size && (long long)nz * count >= 256;
+    return size && (nx <= 64 || (long long)nz * count >= 256);
 }
 
 hipError_t launch_div_fftxy(const Batch& b, int n, int nz, hipStream_t s)

@@ -53,3 +53,18 @@ def test_line_lengths_of_the_transforms(shape):
     G.project()
     assert_close({"u": ru, "v": rv, "w": rw, "p": rp}, gpu_state(G, ("u", "v", "w", "p")),
                  1e-12 * max(1.0, (max(shape) / 256) ** 2), f"{shape}")
+
+
+# Single grids of few square planes, which take the fused plane transforms.  Tolerance as above.
+@pytest.mark.parametrize("n", [16, 24, 32, 48, 64])
+@pytest.mark.parametrize("nz", [8, 10, 48])
+def test_plane_transforms_of_few_planes(n, nz):
+    wl = _wl(n, n, nz, False, "oldroyd_b")
+    u, v, w, B = inputs.random_state(wl.shape, 7, walls=False)
+    s = oracle_solver(wl)
+    s.write_fields(u, v, w, B)
+    ru, rv, rw, rp = oracle.project(s.g, s.u, s.v, s.w, 1.0, s.r.rho)
+    G = gpu_grid(wl)
+    G.write_fields(*to_dev(u, v, w, B))
+    G.project()
+    assert_close({"u": ru, "v": rv, "w": rw, "p": rp}, gpu_state(G, ("u", "v", "w", "p")), 1e-12, f"{n}x{n}x{nz}")
