@@ -115,11 +115,11 @@ hipError_t launch_correct(const Batch& b, int nx, int ny, int nz, hipStream_t s)
 hipError_t launch_copy_ustar(const Batch& b, int nx, int ny, int nz, hipStream_t s);
 hipError_t launch_write_fields(const Desc* d, int precision, long long ncell, int ny, int nx,
                                int walls, int parity, const double* u, const double* v,
-                               const double* w, const double* B6, const double* hist,
+                               const double* w, const double* B6, const double* hist, bool clear,
                                hipStream_t s);
 hipError_t launch_read_fields(const Desc* d, int precision, long long ncell, int parity,
                               unsigned mask, double* u, double* v, double* w, double* p,
-                              double* B6, double* hist, hipStream_t s);
+                              double* B6, double* hist, bool no_hist, hipStream_t s);
 hipError_t launch_health(const Desc* d, int precision, int parity, double* out5, hipStream_t s);
 
 // Guard words after every region of a workspace: a fixed 64-bit pattern, a quiet NaN, so that a

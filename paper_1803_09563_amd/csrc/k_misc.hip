@@ -15,7 +15,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_write(const Desc* Dp, int parity, int walls, int ny,
                                                int nx, const double* u, const double* v,
                                                const double* w, const double* B6,
-                                               const double* hist)
+                                               const double* hist, int clear)
 {
     const Desc& D = *Dp;
     const long long n = D.ncell, ps = D.ps;
@@ -31,19 +31,20 @@ __global__ __launch_bounds__(256) void k_write(const Desc* Dp, int parity, int w
         const double d = (c == 0 || c == 3 || c == 5) ? 1.0 : 0.0;
         Bt[c * ps + q] = (T)(B6[c * n + q] - d);
     }
+    D.p[q] = 0.0;
+    if (!hist && !clear) return;
     T* RT = (T*)D.RT;
     T* RU = (T*)D.RU;
 #pragma unroll
     for (int c = 0; c < 6; ++c) RT[c * ps + q] = hist ? (T)hist[c * n + q] : (T)0;
 #pragma unroll
     for (int c = 0; c < 3; ++c) RU[c * ps + q] = hist ? (T)hist[(6 + c) * n + q] : (T)0;
-    D.p[q] = 0.0;
 }
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_read(const Desc* Dp, int parity, unsigned mask, double* u,
                                               double* v, double* w, double* p, double* B6,
-                                              double* hist)
+                                              double* hist, int no_hist)
 {
     const Desc& D = *Dp;
     const long long n = D.ncell, ps = D.ps;
@@ -65,9 +66,9 @@ __global__ __launch_bounds__(256) void k_read(const Desc* Dp, int parity, unsign
         const T* RT = (const T*)D.RT;
         const T* RU = (const T*)D.RU;
 #pragma unroll
-        for (int c = 0; c < 6; ++c) hist[c * n + q] = (double)RT[c * ps + q];
+        for (int c = 0; c < 6; ++c) hist[c * n + q] = no_hist ? 0.0 : (double)RT[c * ps + q];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) hist[(6 + c) * n + q] = (double)RU[c * ps + q];
+        for (int c = 0; c < 3; ++c) hist[(6 + c) * n + q] = no_hist ? 0.0 : (double)RU[c * ps + q];
     }
 }
 
@@ -205,26 +206,26 @@ hipError_t launch_guard_check(const char* ws, const long long* table, int n, dou
 
 hipError_t launch_write_fields(const Desc* d, int precision, long long ncell, int ny, int nx,
                                int walls, int parity, const double* u, const double* v,
-                               const double* w, const double* B6, const double* hist,
+                               const double* w, const double* B6, const double* hist, bool clear,
                                hipStream_t s)
 {
     dim3 grid((unsigned)((ncell + 255) / 256));
     if (precision == EVP_MIXED)
-        hipLaunchKernelGGL(k_write<float>, grid, dim3(256), 0, s, d, parity, walls, ny, nx, u, v, w, B6, hist);
+        hipLaunchKernelGGL(k_write<float>, grid, dim3(256), 0, s, d, parity, walls, ny, nx, u, v, w, B6, hist, clear ? 1 : 0);
     else
-        hipLaunchKernelGGL(k_write<double>, grid, dim3(256), 0, s, d, parity, walls, ny, nx, u, v, w, B6, hist);
+        hipLaunchKernelGGL(k_write<double>, grid, dim3(256), 0, s, d, parity, walls, ny, nx, u, v, w, B6, hist, clear ? 1 : 0);
     return hipGetLastError();
 }
 
 hipError_t launch_read_fields(const Desc* d, int precision, long long ncell, int parity,
                               unsigned mask, double* u, double* v, double* w, double* p,
-                              double* B6, double* hist, hipStream_t s)
+                              double* B6, double* hist, bool no_hist, hipStream_t s)
 {
     dim3 grid((unsigned)((ncell + 255) / 256));
     if (precision == EVP_MIXED)
-        hipLaunchKernelGGL(k_read<float>, grid, dim3(256), 0, s, d, parity, mask, u, v, w, p, B6, hist);
+        hipLaunchKernelGGL(k_read<float>, grid, dim3(256), 0, s, d, parity, mask, u, v, w, p, B6, hist, no_hist ? 1 : 0);
     else
-        hipLaunchKernelGGL(k_read<double>, grid, dim3(256), 0, s, d, parity, mask, u, v, w, p, B6, hist);
+        hipLaunchKernelGGL(k_read<double>, grid, dim3(256), 0, s, d, parity, mask, u, v, w, p, B6, hist, no_hist ? 1 : 0);
     return hipGetLastError();
 }
 
