@@ -102,7 +102,7 @@ Layout make_layout(int nx, int ny, int nz, int bc_y, int precision)
         }
         return o;
     };
-    L.desc = take(4096);
+    L.desc = take(evp::kDescBytes);
     L.u = take(n * 8); L.v = take(n * 8); L.w = take(n * 8);
     L.us = take(n * 8); L.vs = take(n * 8); L.ws = take(n * 8);
     L.p = take(n * 8);
@@ -141,7 +141,6 @@ struct evp_grid {
     int parity;
     int integrator;    // EVP_AB2 or EVP_RK3
     bool have_hist, have_rheo, have_fields;
-    bool hist_zero;               // the history is zero, whatever RT and RU hold (fields written without one)
     double rho_single;            // rho of evp_set_rheology (the descriptor holds rho_0 in two-phase mode)
     bool two_phase;               // Sec. 3.2 path on
     evp_two_phase_t tp;
@@ -169,6 +168,7 @@ template <typename T> void stage_constants(evp::StageConst<T>& k, const Desc& h)
 
 int upload_desc(evp_grid* g)
 {
+    static_assert(sizeof(Desc) + sizeof(double) <= evp::kDescBytes, "the descriptor and its flag fit their region");
     stage_constants(g->h.kd, g->h);
     stage_constants(g->h.kf, g->h);
     hipError_t e = hipMemcpyAsync(g->d, &g->h, sizeof(Desc), hipMemcpyHostToDevice, g->stream);
@@ -378,6 +378,8 @@ int predictor_by_model(evp_grid* const* gs, const Batch& b, bool freeze, bool rk
             if (two_phase) {
                 // FP64 and Adams-Bashforth only (evp_set_two_phase, evp_step_rk3 see to it)
                 if (g0->precision != EVP_FP64 || rk3) return hipErrorInvalidValue;
+                for (int i = 0; i < bm.count; ++i)
+                    if (hipError_t e = evp::launch_fill(evp::hist_zero(bm.d[i]), 1, 0.0, g0->stream)) return e;
                 return evp::launch_stress_two_phase(bm, g0->nx, g0->ny, g0->nz, g0->stream, g0->bc == EVP_WALLS, model, houc);
             }
             if (g0->precision == EVP_MIXED)
@@ -385,7 +387,6 @@ int predictor_by_model(evp_grid* const* gs, const Batch& b, bool freeze, bool rk
             return evp::launch_predictor_fp64(bm, g0->nx, g0->ny, g0->nz, freeze, g0->stream, model, rk3, houc);
         });
     }
-    for (int i = 0; i < b.count; ++i) gs[i]->hist_zero = false;
     return r;
 }
 
@@ -659,6 +660,7 @@ int create_in(int nx, int ny, int nz, double lx, double ly, double lz, int bc_y,
     // zero state (u = 0, B - I = 0, histories 0, p = 0; the region is a whole number of 256-byte
     // blocks) and upload tables
     hipError_t e = evp::launch_fill((double*)(w + L.u), (long long)((L.spec - L.u) / 8), 0.0, g->stream);
+    if (e == hipSuccess) e = evp::launch_fill(evp::hist_zero(g->d), 1, 0.0, g->stream);
     if (e != hipSuccess) { delete g; return hip_fail(e, "workspace clear"); }
     std::vector<char> tables;
     build_tables(g, tables, L.twx);
@@ -901,8 +903,8 @@ int evp_write_fields(evp_grid* g, const double* u, const double* v, const double
     if (!u || !v || !w || !B6) return fail(EVP_ERR_ARG, "u, v, w and B6 must be non-NULL");
     // Without a history the next step takes none, so the nine planes of zeros that stand for it are not
     // stored: reads and saved states give zeros until a step writes the histories (writing, projecting and
-    // reading 240x120x160: 394 -> 324 us).
-    // A graph may be replayed at any state of the grid: under capture they are stored.
+    // reading 240x120x160: 394 -> 324 us).  A captured write stores them: it can be replayed between steps
+    // that do take a history.
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (!hist && hipStreamIsCapturing(g->stream, &cap) != hipSuccess) cap = hipStreamCaptureStatusActive;
     const bool clear = !hist && cap != hipStreamCaptureStatusNone;
@@ -910,7 +912,6 @@ int evp_write_fields(evp_grid* g, const double* u, const double* v, const double
                                             g->h.walls, g->parity, u, v, w, B6, hist, clear, g->stream);
     if (e != hipSuccess) return hip_fail(e, "write_fields");
     g->have_hist = hist != nullptr;
-    g->hist_zero = !hist && !clear;
     g->have_fields = true;
     g->nstep = 0;
     g->p_hist = false;
@@ -991,7 +992,7 @@ int evp_read_fields(evp_grid* g, unsigned mask, double* u, double* v, double* w,
         return fail(EVP_ERR_ARG, "a selected output pointer is NULL");
     if (mask == 0) return EVP_OK;
     hipError_t e = evp::launch_read_fields(g->d, g->precision, g->h.ncell, g->parity, mask, u, v,
-                                           w, p, B6, hist, g->hist_zero, g->stream);
+                                           w, p, B6, hist, g->stream);
     if (e != hipSuccess) return hip_fail(e, "read_fields");
     return EVP_OK;
 }
@@ -1066,11 +1067,9 @@ int evp_save_state(evp_grid* g, void* dst, size_t bytes)
     if (e == hipSuccess) e = hipMemcpyAsync(d + o, B, L.B1 - L.B0, hipMemcpyDeviceToDevice, g->stream);
     o += L.B1 - L.B0;
     if (e == hipSuccess) e = hipMemcpyAsync(d + o, g->ws + L.RT, L.spec - L.RT, hipMemcpyDeviceToDevice, g->stream);
-    if (g->hist_zero) {
-        const long long plane8 = L.ps * (g->precision == EVP_MIXED ? 4 : 8) / 8;
-        if (e == hipSuccess) e = evp::launch_fill((double*)(d + o), 6 * plane8, 0.0, g->stream);
-        if (e == hipSuccess) e = evp::launch_fill((double*)(d + o + (L.RU - L.RT)), 3 * plane8, 0.0, g->stream);
-    }
+    const long long plane8 = L.ps * (g->precision == EVP_MIXED ? 4 : 8) / 8;
+    if (e == hipSuccess) e = evp::launch_saved_history(g->d, (double*)(d + o), 6 * plane8, g->stream);
+    if (e == hipSuccess) e = evp::launch_saved_history(g->d, (double*)(d + o + (L.RU - L.RT)), 3 * plane8, g->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
     if (e != hipSuccess) return hip_fail(e, "save_state");
     return EVP_OK;
@@ -1096,10 +1095,10 @@ int evp_load_state(evp_grid* g, const void* src, size_t bytes)
     if (e == hipSuccess) e = hipMemcpyAsync(g->ws + (g->parity ? L.B1 : L.B0), s + o, L.B1 - L.B0, hipMemcpyDeviceToDevice, g->stream);
     o += L.B1 - L.B0;
     if (e == hipSuccess) e = hipMemcpyAsync(g->ws + L.RT, s + o, L.spec - L.RT, hipMemcpyDeviceToDevice, g->stream);
+    if (e == hipSuccess) e = evp::launch_fill(evp::hist_zero(g->d), 1, 0.0, g->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
     if (e != hipSuccess) return hip_fail(e, "load_state");
     g->have_hist = hd.have_hist != 0;
-    g->hist_zero = false;
     g->nstep = hd.nstep;
     g->have_fields = true;
     return EVP_OK;

@@ -73,6 +73,12 @@ struct Batch {
 #define EVP_GLOBAL __attribute__((address_space(1)))
 template <typename T> using gptr = EVP_GLOBAL T*;
 
+// Device flag of a grid, in the last 8 bytes of its descriptor's region: not 0 while the history is zero
+// whatever RT and RU hold (set by a write without a history, cleared by the predictor).  On the device, so
+// that replayed graphs keep it too.
+constexpr int kDescBytes = 4096;
+__host__ __device__ inline double* hist_zero(const Desc* d) { return (double*)((char*)d + kDescBytes) - 1; }
+
 constexpr int ST_PARITY = 1;
 constexpr int ST_EULER = 2;
 constexpr int ST_PZERO = 4;      // two-phase: no pressure history yet (2 p^n - p^{n-1} := 0)
@@ -119,7 +125,8 @@ hipError_t launch_write_fields(const Desc* d, int precision, long long ncell, in
                                hipStream_t s);
 hipError_t launch_read_fields(const Desc* d, int precision, long long ncell, int parity,
                               unsigned mask, double* u, double* v, double* w, double* p,
-                              double* B6, double* hist, bool no_hist, hipStream_t s);
+                              double* B6, double* hist, hipStream_t s);
+hipError_t launch_saved_history(const Desc* d, double* p, long long n, hipStream_t s);
 hipError_t launch_health(const Desc* d, int precision, int parity, double* out5, hipStream_t s);
 
 // Guard words after every region of a workspace: a fixed 64-bit pattern, a quiet NaN, so that a

@@ -32,6 +32,7 @@ __global__ __launch_bounds__(256) void k_write(const Desc* Dp, int parity, int w
         Bt[c * ps + q] = (T)(B6[c * n + q] - d);
     }
     D.p[q] = 0.0;
+    if (q == 0) *hist_zero(Dp) = !hist && !clear ? 1.0 : 0.0;
     if (!hist && !clear) return;
     T* RT = (T*)D.RT;
     T* RU = (T*)D.RU;
@@ -44,7 +45,7 @@ __global__ __launch_bounds__(256) void k_write(const Desc* Dp, int parity, int w
 template <typename T>
 __global__ __launch_bounds__(256) void k_read(const Desc* Dp, int parity, unsigned mask, double* u,
                                               double* v, double* w, double* p, double* B6,
-                                              double* hist, int no_hist)
+                                              double* hist)
 {
     const Desc& D = *Dp;
     const long long n = D.ncell, ps = D.ps;
@@ -63,13 +64,21 @@ __global__ __launch_bounds__(256) void k_read(const Desc* Dp, int parity, unsign
         }
     }
     if (mask & EVP_READ_HIST) {
+        const bool zero = *hist_zero(Dp) != 0.0;
         const T* RT = (const T*)D.RT;
         const T* RU = (const T*)D.RU;
 #pragma unroll
-        for (int c = 0; c < 6; ++c) hist[c * n + q] = no_hist ? 0.0 : (double)RT[c * ps + q];
+        for (int c = 0; c < 6; ++c) hist[c * n + q] = zero ? 0.0 : (double)RT[c * ps + q];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) hist[(6 + c) * n + q] = no_hist ? 0.0 : (double)RU[c * ps + q];
+        for (int c = 0; c < 3; ++c) hist[(6 + c) * n + q] = zero ? 0.0 : (double)RU[c * ps + q];
     }
+}
+
+// n values of a saved state's history: zeros if the grid's history is zero
+__global__ __launch_bounds__(256) void k_saved_history(const Desc* Dp, double* p, long long n)
+{
+    const long long q = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (q < n && *hist_zero(Dp) != 0.0) p[q] = 0.0;
 }
 
 // per-block partials: [nonfinite, det_le0, trace_ge95, max_div, energy]
@@ -217,15 +226,21 @@ hipError_t launch_write_fields(const Desc* d, int precision, long long ncell, in
     return hipGetLastError();
 }
 
+hipError_t launch_saved_history(const Desc* d, double* p, long long n, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_saved_history, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, d, p, n);
+    return hipGetLastError();
+}
+
 hipError_t launch_read_fields(const Desc* d, int precision, long long ncell, int parity,
                               unsigned mask, double* u, double* v, double* w, double* p,
-                              double* B6, double* hist, bool no_hist, hipStream_t s)
+                              double* B6, double* hist, hipStream_t s)
 {
     dim3 grid((unsigned)((ncell + 255) / 256));
     if (precision == EVP_MIXED)
-        hipLaunchKernelGGL(k_read<float>, grid, dim3(256), 0, s, d, parity, mask, u, v, w, p, B6, hist, no_hist ? 1 : 0);
+        hipLaunchKernelGGL(k_read<float>, grid, dim3(256), 0, s, d, parity, mask, u, v, w, p, B6, hist);
     else
-        hipLaunchKernelGGL(k_read<double>, grid, dim3(256), 0, s, d, parity, mask, u, v, w, p, B6, hist, no_hist ? 1 : 0);
+        hipLaunchKernelGGL(k_read<double>, grid, dim3(256), 0, s, d, parity, mask, u, v, w, p, B6, hist);
     return hipGetLastError();
 }
 

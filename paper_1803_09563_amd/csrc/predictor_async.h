@@ -193,6 +193,8 @@ __device__ __forceinline__ void march(SmemA<T, TX, TY, MODEL == EVP_FENE_P>& S, 
     const int hwave = wave & (TL::NC / 64 - 1);          // wave of this half
     const unsigned o8 = (unsigned)oij * 8u, oT = (unsigned)oij * (unsigned)sizeof(T);
 
+    if (HALF == 0 && blockIdx.x == 0 && threadIdx.x == 0) *hist_zero(B.d[b]) = 0.0;     // this launch writes the histories
+
     const int st = B.state[b];
     // fields of this half: its components of B and RT, its rows of RU, its predicted velocities
     const gptr<const T> Bin = (gptr<const T>)D.Bt[st & 1] + (long long)C0 * ps;

@@ -1,5 +1,7 @@
 """Fields written without a history: the history reads as zero, is saved as zero and is not used by the
 next step, whatever an earlier run left in its place; a captured write clears it on every replay."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -71,3 +73,28 @@ def test_captured_write_clears_the_history():
         g.replay()
         torch.cuda.synchronize()
         assert not G.read_fields(("hist",))["hist"].any()
+
+
+def test_captured_read_of_the_history_follows_the_grid():
+    import torch
+    import paper_1803_09563_amd as evp
+    wl = _wl(16, 16, 16, False, "oldroyd_b")
+    f = to_dev(*_fields(wl, 4))
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    G = gpu_grid(wl, stream=s)
+    G.write_fields(*f)
+    out = torch.empty((9,) + wl.shape, dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        assert evp.lib.evp_read_fields(G.handle, evp.READ_HIST, None, None, None, None, None, ctypes.c_void_p(out.data_ptr())) == 0
+    for steps in (0, 1, 0, 2):
+        if steps:
+            G.step(1e-3, steps)
+        else:
+            G.write_fields(*f)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, G.read_fields(("hist",))["hist"])
+        assert bool(out.any()) == (steps > 0)
