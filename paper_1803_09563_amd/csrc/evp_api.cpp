@@ -906,7 +906,10 @@ int evp_write_fields(evp_grid* g, const double* u, const double* v, const double
     // reading 240x120x160: 394 -> 324 us).  A captured write stores them: it can be replayed between steps
     // that do take a history.
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (!hist && hipStreamIsCapturing(g->stream, &cap) != hipSuccess) cap = hipStreamCaptureStatusActive;
+    if (!hist && hipStreamIsCapturing(g->stream, &cap) != hipSuccess) {
+        (void)hipGetLastError();      // the write itself reports what is wrong with the stream
+        cap = hipStreamCaptureStatusActive;
+    }
     const bool clear = !hist && cap != hipStreamCaptureStatusNone;
     hipError_t e = evp::launch_write_fields(g->d, g->precision, g->h.ncell, g->ny, g->nx,
                                             g->h.walls, g->parity, u, v, w, B6, hist, clear, g->stream);

@@ -94,6 +94,7 @@ def test_captured_read_of_the_history_follows_the_grid():
             G.step(1e-3, steps)
         else:
             G.write_fields(*f)
+        torch.cuda.synchronize()      # the replay runs on the current stream, the grid on its own
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, G.read_fields(("hist",))["hist"])

@@ -122,3 +122,26 @@ def test_mixed_batch_tiles_equal_single_bitwise(adv, walls):
         sa, sc = gpu_state(a), gpu_state(c)
         for k in sa:
             assert np.array_equal(sa[k], sc[k]), k
+
+
+# the kernel for several models in its narrow tiles, with rows in groups of 16 bytes and value by value
+@pytest.mark.parametrize("walls", [False, True])
+@pytest.mark.parametrize("shape", [(16, 12, 10), (10, 12, 8)])
+def test_models_in_one_launch_equal_single_bitwise(shape, walls):
+    import paper_1803_09563_amd as evp
+    singles, batched = [], []
+    for b in range(4):
+        wl, fields = _stage(shape, ("saramito", "fene_p", "oldroyd_b", "oldroyd_b")[b], walls, seed=300 + b)
+        if b == 3:
+            wl.model = evp.NEO_HOOKEAN
+        a, c = gpu_grid(wl, precision=evp.MIXED), gpu_grid(wl, precision=evp.MIXED)
+        for G in (a, c):
+            G.write_fields(*to_dev(*fields))
+        a.step(1e-3, 2)
+        singles.append(a)
+        batched.append(c)
+    evp.step_batch(batched, 1e-3, 2)
+    for a, c in zip(singles, batched):
+        sa, sc = gpu_state(a), gpu_state(c)
+        for k in sa:
+            assert np.array_equal(sa[k], sc[k]), k
