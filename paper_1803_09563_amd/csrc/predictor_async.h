@@ -21,10 +21,10 @@
 // them into the ring before the barrier of the middle; the cell's own FP64 velocity is kept from there
 // for the update of the plane after.
 //
-// What bounds it: in FP64 at 512x256x256 the vector ALU (1.47k instructions per cell and plane, busy 0.6 of
-// the cycles at the 2.1 GHz the chip holds under this load) and memory (11-12 GB a launch, 4.4 TB/s)
-// are about equal, and neither hides fully behind the other.  The mixed form is bound by the vector ALU
-// (1.5k instructions, FP32 runs at the rate of FP64 here; busy 0.85 at 128^3).  Against the synchronously
+// What bounds it: in FP64 at 512x256x256 the vector ALU (1.4k instructions per cell and plane, busy 0.6 of
+// the cycles at the 2.1 GHz the chip holds under this load) and memory (12.5 GB a launch, 5.0 TB/s, above a
+// plain copy's 4.8) are about equal, and neither hides fully behind the other.  The mixed form is bound by
+// the vector ALU (1.4k instructions, FP32 runs at the rate of FP64 here; busy all the time).  Against the synchronously
 // staged form before it (one thread per cell, FP64: two waves per SIMD and three exposed memory round
 // trips a plane; mixed: four waves, the rows beside a wall in a kernel of their own on a second stream):
 // FP64 Saramito 2970 -> 2510 us at 512x256x256, 457 -> 309 at 256x128x128 (a Runge-Kutta substep), 180 -> 154
