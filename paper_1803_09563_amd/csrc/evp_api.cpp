@@ -168,7 +168,7 @@ template <typename T> void stage_constants(evp::StageConst<T>& k, const Desc& h)
 
 int upload_desc(evp_grid* g)
 {
-    static_assert(sizeof(Desc) + sizeof(double) <= evp::kDescBytes, "the descriptor and its flag fit their region");
+    static_assert(sizeof(Desc) + 2 * sizeof(double) <= evp::kDescBytes, "the descriptor and its note fit their region");
     stage_constants(g->h.kd, g->h);
     stage_constants(g->h.kf, g->h);
     hipError_t e = hipMemcpyAsync(g->d, &g->h, sizeof(Desc), hipMemcpyHostToDevice, g->stream);
@@ -355,6 +355,14 @@ int predictor_by_model(evp_grid* const* gs, const Batch& b, bool freeze, bool rk
     int r = EVP_OK;
     constexpr int kModels = EVP_NEO_HOOKEAN + 1;
     const bool together = g0->precision == EVP_MIXED && !rk3;
+    // the two-phase kernels read RT and RU themselves: a history noted to be zero is stored first
+    for (int i = 0; two_phase && i < b.count; ++i) {
+        const Desc& h = gs[i]->h;
+        hipError_t e = evp::launch_saved_history(b.d[i], (double*)h.RT, 6 * h.ps, g0->stream);
+        if (e == hipSuccess) e = evp::launch_saved_history(b.d[i], (double*)h.RU, 3 * h.ps, g0->stream);
+        if (e == hipSuccess) e = evp::launch_fill(evp::hist_zero(b.d[i]), 1, 0.0, g0->stream);
+        if (e != hipSuccess) return hip_fail(e, "two-phase history");
+    }
     for (int variant = 0; variant < 2 * kModels && !r; ++variant) {
         const int adv = variant / kModels;
         int model = variant % kModels;
@@ -378,8 +386,6 @@ int predictor_by_model(evp_grid* const* gs, const Batch& b, bool freeze, bool rk
             if (two_phase) {
                 // FP64 and Adams-Bashforth only (evp_set_two_phase, evp_step_rk3 see to it)
                 if (g0->precision != EVP_FP64 || rk3) return hipErrorInvalidValue;
-                for (int i = 0; i < bm.count; ++i)
-                    if (hipError_t e = evp::launch_fill(evp::hist_zero(bm.d[i]), 1, 0.0, g0->stream)) return e;
                 return evp::launch_stress_two_phase(bm, g0->nx, g0->ny, g0->nz, g0->stream, g0->bc == EVP_WALLS, model, houc);
             }
             if (g0->precision == EVP_MIXED)
@@ -660,7 +666,7 @@ int create_in(int nx, int ny, int nz, double lx, double ly, double lz, int bc_y,
     // zero state (u = 0, B - I = 0, histories 0, p = 0; the region is a whole number of 256-byte
     // blocks) and upload tables
     hipError_t e = evp::launch_fill((double*)(w + L.u), (long long)((L.spec - L.u) / 8), 0.0, g->stream);
-    if (e == hipSuccess) e = evp::launch_fill(evp::hist_zero(g->d), 1, 0.0, g->stream);
+    if (e == hipSuccess) e = evp::launch_fill(evp::hist_zero(g->d) - 1, 2, 0.0, g->stream);     // and its readers
     if (e != hipSuccess) { delete g; return hip_fail(e, "workspace clear"); }
     std::vector<char> tables;
     build_tables(g, tables, L.twx);
@@ -901,18 +907,11 @@ int evp_write_fields(evp_grid* g, const double* u, const double* v, const double
 {
     if (int r = check_grid(g)) return r;
     if (!u || !v || !w || !B6) return fail(EVP_ERR_ARG, "u, v, w and B6 must be non-NULL");
-    // Without a history the next step takes none, so the nine planes of zeros that stand for it are not
-    // stored: reads and saved states give zeros until a step writes the histories (writing, projecting and
-    // reading 240x120x160: 394 -> 324 us).  A captured write stores them: it can be replayed between steps
-    // that do take a history.
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (!hist && hipStreamIsCapturing(g->stream, &cap) != hipSuccess) {
-        (void)hipGetLastError();      // the write itself reports what is wrong with the stream
-        cap = hipStreamCaptureStatusActive;
-    }
-    const bool clear = !hist && cap != hipStreamCaptureStatusNone;
+    // Without a history the nine planes of zeros that stand for it are not stored, only noted: steps (also
+    // replayed ones), reads and saved states take zeros until a step writes the histories (writing,
+    // projecting and reading 240x120x160: 394 -> 324 us).
     hipError_t e = evp::launch_write_fields(g->d, g->precision, g->h.ncell, g->ny, g->nx,
-                                            g->h.walls, g->parity, u, v, w, B6, hist, clear, g->stream);
+                                            g->h.walls, g->parity, u, v, w, B6, hist, g->stream);
     if (e != hipSuccess) return hip_fail(e, "write_fields");
     g->have_hist = hist != nullptr;
     g->have_fields = true;

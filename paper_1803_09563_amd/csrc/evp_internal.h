@@ -73,11 +73,13 @@ struct Batch {
 #define EVP_GLOBAL __attribute__((address_space(1)))
 template <typename T> using gptr = EVP_GLOBAL T*;
 
-// Device flag of a grid, in the last 8 bytes of its descriptor's region: not 0 while the history is zero
-// whatever RT and RU hold (set by a write without a history, cleared by the predictor).  On the device, so
-// that replayed graphs keep it too.
+// Note of a grid, in the last 8 bytes of its descriptor's region: not 0 while the history is zero whatever
+// RT and RU hold (set by a write without a history).  On the device, because a captured step is replayed
+// between writes that the host cannot foresee: the predictor reads it and clears it once all of its blocks
+// have, which they count in the word before (0 between launches).
 constexpr int kDescBytes = 4096;
 __host__ __device__ inline double* hist_zero(const Desc* d) { return (double*)((char*)d + kDescBytes) - 1; }
+__host__ __device__ inline unsigned* hist_readers(const Desc* d) { return (unsigned*)(hist_zero(d) - 1); }
 
 constexpr int ST_PARITY = 1;
 constexpr int ST_EULER = 2;
@@ -121,7 +123,7 @@ hipError_t launch_correct(const Batch& b, int nx, int ny, int nz, hipStream_t s)
 hipError_t launch_copy_ustar(const Batch& b, int nx, int ny, int nz, hipStream_t s);
 hipError_t launch_write_fields(const Desc* d, int precision, long long ncell, int ny, int nx,
                                int walls, int parity, const double* u, const double* v,
-                               const double* w, const double* B6, const double* hist, bool clear,
+                               const double* w, const double* B6, const double* hist,
                                hipStream_t s);
 hipError_t launch_read_fields(const Desc* d, int precision, long long ncell, int parity,
                               unsigned mask, double* u, double* v, double* w, double* p,

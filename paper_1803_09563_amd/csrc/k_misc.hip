@@ -15,7 +15,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_write(const Desc* Dp, int parity, int walls, int ny,
                                                int nx, const double* u, const double* v,
                                                const double* w, const double* B6,
-                                               const double* hist, int clear)
+                                               const double* hist)
 {
     const Desc& D = *Dp;
     const long long n = D.ncell, ps = D.ps;
@@ -32,14 +32,14 @@ __global__ __launch_bounds__(256) void k_write(const Desc* Dp, int parity, int w
         Bt[c * ps + q] = (T)(B6[c * n + q] - d);
     }
     D.p[q] = 0.0;
-    if (q == 0) *hist_zero(Dp) = !hist && !clear ? 1.0 : 0.0;
-    if (!hist && !clear) return;
+    if (q == 0) *hist_zero(Dp) = hist ? 0.0 : 1.0;
+    if (!hist) return;
     T* RT = (T*)D.RT;
     T* RU = (T*)D.RU;
 #pragma unroll
-    for (int c = 0; c < 6; ++c) RT[c * ps + q] = hist ? (T)hist[c * n + q] : (T)0;
+    for (int c = 0; c < 6; ++c) RT[c * ps + q] = (T)hist[c * n + q];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) RU[c * ps + q] = hist ? (T)hist[(6 + c) * n + q] : (T)0;
+    for (int c = 0; c < 3; ++c) RU[c * ps + q] = (T)hist[(6 + c) * n + q];
 }
 
 template <typename T>
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(256) void k_read(const Desc* Dp, int parity, unsign
     }
 }
 
-// n values of a saved state's history: zeros if the grid's history is zero
+// n values of a history: zeros if the grid's history is noted to be zero
 __global__ __launch_bounds__(256) void k_saved_history(const Desc* Dp, double* p, long long n)
 {
     const long long q = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -215,14 +215,14 @@ hipError_t launch_guard_check(const char* ws, const long long* table, int n, dou
 
 hipError_t launch_write_fields(const Desc* d, int precision, long long ncell, int ny, int nx,
                                int walls, int parity, const double* u, const double* v,
-                               const double* w, const double* B6, const double* hist, bool clear,
+                               const double* w, const double* B6, const double* hist,
                                hipStream_t s)
 {
     dim3 grid((unsigned)((ncell + 255) / 256));
     if (precision == EVP_MIXED)
-        hipLaunchKernelGGL(k_write<float>, grid, dim3(256), 0, s, d, parity, walls, ny, nx, u, v, w, B6, hist, clear ? 1 : 0);
+        hipLaunchKernelGGL(k_write<float>, grid, dim3(256), 0, s, d, parity, walls, ny, nx, u, v, w, B6, hist);
     else
-        hipLaunchKernelGGL(k_write<double>, grid, dim3(256), 0, s, d, parity, walls, ny, nx, u, v, w, B6, hist, clear ? 1 : 0);
+        hipLaunchKernelGGL(k_write<double>, grid, dim3(256), 0, s, d, parity, walls, ny, nx, u, v, w, B6, hist);
     return hipGetLastError();
 }
 

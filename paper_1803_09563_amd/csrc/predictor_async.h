@@ -193,8 +193,6 @@ __device__ __forceinline__ void march(SmemA<T, TX, TY, MODEL == EVP_FENE_P>& S, 
     const int hwave = wave & (TL::NC / 64 - 1);          // wave of this half
     const unsigned o8 = (unsigned)oij * 8u, oT = (unsigned)oij * (unsigned)sizeof(T);
 
-    if (HALF == 0 && blockIdx.x == 0 && threadIdx.x == 0) *hist_zero(B.d[b]) = 0.0;     // this launch writes the histories
-
     const int st = B.state[b];
     // fields of this half: its components of B and RT, its rows of RU, its predicted velocities
     const gptr<const T> Bin = (gptr<const T>)D.Bt[st & 1] + (long long)C0 * ps;
@@ -373,9 +371,28 @@ __device__ __forceinline__ void march(SmemA<T, TX, TY, MODEL == EVP_FENE_P>& S, 
         stage_own(1, wm[2]);
         stage_own(0, w0);
     }
+    // the grid's note that its history is zero: a plain load, and the only one, because another block clears
+    // the note later in this launch (the high word of 0.0 or 1.0); it travels with the requests above
+    int note = *(gptr<const volatile int>)((gptr<const int>)hist_zero(B.d[b]) + 1);
     arrive<0>();
+    __asm__ volatile("" : "+v"(note));
     round_v(k0 % 3);
+    // no history: none is taken, the histories' memory may hold anything
+    const bool none = euler || __builtin_amdgcn_readfirstlane(note) != 0;
     lds_barrier();
+    // this launch writes the histories, so the note goes: at an Euler step, where no block reads it, at
+    // once, otherwise when the last block has read it
+    if (HALF == 0 && threadIdx.x == 0 && none) {
+        if (euler) {
+            if (blockIdx.x == 0) *(gptr<double>)hist_zero(B.d[b]) = 0.0;
+        } else {
+            const gptr<unsigned> readers = (gptr<unsigned>)hist_readers(B.d[b]);
+            if (__hip_atomic_fetch_add(readers, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1) {
+                *readers = 0u;
+                *(gptr<double>)hist_zero(B.d[b]) = 0.0;
+            }
+        }
+    }
     if (wall_tile) {
         if constexpr (!MIXED) ghosts(1, (k0 + 2) % 3, true);
         else ghosts(1, 0, false);
@@ -639,11 +656,11 @@ __device__ __forceinline__ void march(SmemA<T, TX, TY, MODEL == EVP_FENE_P>& S, 
                 // RK3 keeps the advection as the history; the stress divergence at B^k and any solid
                 // penalisation follow in k_stress_div
                 ru[0] = ax;
-                rs[0] = U0 + (double)(dt * (((T)2 * cal * (ms * lx + fx) + cal * tt) * irho - c1 * ax - (euler ? (T)0 : c2 * oru[0])));
+                rs[0] = U0 + (double)(dt * (((T)2 * cal * (ms * lx + fx) + cal * tt) * irho - c1 * ax - (none ? (T)0 : c2 * oru[0])));
             } else {
                 // a solid, if any, is applied by k_penalise once u* is complete
                 ru[0] = -ax + (ms * lx + tt + fx) * irho;
-                rs[0] = U0 + (double)(dt * (c1 * ru[0] + (euler ? (T)0 : c2 * oru[0])));
+                rs[0] = U0 + (double)(dt * (c1 * ru[0] + (none ? (T)0 : c2 * oru[0])));
             }
             if (freeze) { rs[0] = U0; ru[0] = (T)0; }
         } else {
@@ -678,13 +695,13 @@ __device__ __forceinline__ void march(SmemA<T, TX, TY, MODEL == EVP_FENE_P>& S, 
             if constexpr (RK3) {
                 ru[0] = ay;
                 ru[NF - 1] = az;
-                rs[0] = V0 + (double)(dt * (((T)2 * cal * (ms * ly) + cal * ty_) * irho - c1 * ay - (euler ? (T)0 : c2 * oru[0])));
-                rs[NF - 1] = W0 + (double)(dt * (((T)2 * cal * (ms * lz) + cal * tz_) * irho - c1 * az - (euler ? (T)0 : c2 * oru[NF - 1])));
+                rs[0] = V0 + (double)(dt * (((T)2 * cal * (ms * ly) + cal * ty_) * irho - c1 * ay - (none ? (T)0 : c2 * oru[0])));
+                rs[NF - 1] = W0 + (double)(dt * (((T)2 * cal * (ms * lz) + cal * tz_) * irho - c1 * az - (none ? (T)0 : c2 * oru[NF - 1])));
             } else {
                 ru[0] = -ay + (ms * ly + ty_) * irho;
                 ru[NF - 1] = -az + (ms * lz + tz_) * irho;
-                rs[0] = V0 + (double)(dt * (c1 * ru[0] + (euler ? (T)0 : c2 * oru[0])));
-                rs[NF - 1] = W0 + (double)(dt * (c1 * ru[NF - 1] + (euler ? (T)0 : c2 * oru[NF - 1])));
+                rs[0] = V0 + (double)(dt * (c1 * ru[0] + (none ? (T)0 : c2 * oru[0])));
+                rs[NF - 1] = W0 + (double)(dt * (c1 * ru[NF - 1] + (none ? (T)0 : c2 * oru[NF - 1])));
             }
             if (vwall) { rs[0] = 0.0; ru[0] = (T)0; }
             if (freeze) {
@@ -695,7 +712,7 @@ __device__ __forceinline__ void march(SmemA<T, TX, TY, MODEL == EVP_FENE_P>& S, 
         }
 #pragma unroll
         for (int cc = 0; cc < 3; ++cc) {
-            rb[cc] = wm[2][cc] + dt * (c1 * rt[cc] + (euler ? (T)0 : c2 * old[cc]));
+            rb[cc] = wm[2][cc] + dt * (c1 * rt[cc] + (none ? (T)0 : c2 * old[cc]));
         }
         keep_v();
 #undef U0
