@@ -155,7 +155,8 @@ def _dptr(t, shape, name):
 class Grid:
     """One solve: nx x ny x nz cells in an lx x ly x lz box (walls=True: no-slip walls at
     y = -ly/2, +ly/2), FP64 or MIXED precision.  Device memory is one torch uint8 tensor; work is
-    enqueued on ``stream`` (a torch.cuda.Stream; default: the current stream).
+    enqueued on ``stream`` (a torch.cuda.Stream; default: the current stream).  What a read returns
+    may be used on the caller's current stream at once.
     static_workspace=True creates the grid with evp_create_grid_static instead: no device memory
     is allocated, the grid lives in the library's static workspace of the current device (one
     such grid per device at a time, at most STATIC_WORKSPACE_BYTES)."""
@@ -209,6 +210,21 @@ class Grid:
             if buf is not None:
                 buf.record_stream(stream)
         self.stream = stream
+
+    def _hand_over(self, tensors):
+        """Order the caller's current stream after the grid's, which fills these tensors of its own,
+        and keep their memory from the grid's later reads until the current stream is done with them.
+        Streams under capture are left to the capture, which orders its own forks and joins."""
+        torch = _torch()
+        cur = torch.cuda.current_stream(self.device)
+        if cur == self.stream or torch.cuda.is_current_stream_capturing():
+            return
+        with torch.cuda.stream(self.stream):
+            if torch.cuda.is_current_stream_capturing():
+                return
+        cur.wait_stream(self.stream)
+        for t in tensors:
+            t.record_stream(cur)
 
     def set_rheology(self, model, rho=1.0, mu_s=0.0, mu_p=0.0, lam=1.0, tau_y=0.0, L2=1.0e4):
         _check(lib.evp_set_rheology(self._h, int(model), rho, mu_s, mu_p, lam, tau_y, L2),
@@ -264,6 +280,7 @@ class Grid:
         with torch.cuda.stream(self.stream):
             out = torch.empty(self.shape, dtype=torch.float64, device=self.device)
         _check(lib.evp_read_level_set(self._h, ctypes.c_void_p(out.data_ptr())), "evp_read_level_set")
+        self._hand_over([out])
         return out
 
     def set_forcing(self, kind, amp=0.0, ky=0.0):
@@ -305,6 +322,7 @@ class Grid:
         ptr = lambda k: ctypes.c_void_p(out[k].data_ptr()) if k in out else None
         _check(lib.evp_read_fields(self._h, mask, ptr("u"), ptr("v"), ptr("w"), ptr("p"),
                                    ptr("B"), ptr("hist")), "evp_read_fields")
+        self._hand_over(out.values())
         return out
 
     def save_state(self):
@@ -316,6 +334,7 @@ class Grid:
         off = (-buf.data_ptr()) % 256
         view = buf[off:off + n]
         _check(lib.evp_save_state(self._h, ctypes.c_void_p(view.data_ptr()), n), "evp_save_state")
+        self._hand_over([buf])
         return view
 
     def load_state(self, state):
