@@ -585,14 +585,15 @@ __device__ __forceinline__ void march(SmemA<T, TX, TY, MODEL == EVP_FENE_P>& S, 
         // ---- second part: upper-convected terms, momentum (every lane; only valid cells are
         // stored).  e, w, n, s, f, b: the +x, -x, +y, -y, +z, -z neighbours ----
         const int f0 = k & 1, f1 = (k + 1) & 1;
-#define TAU(buf, ff, cc, di, dj) (fene ? S.F[ff][rV + (dj)][cV + (di)] * (((cc) == 0 || (cc) == 3 || (cc) == 5) \
-                                      ? S.B[buf][cc][rB + (dj)][cB + (di)] + (T)1 : S.B[buf][cc][rB + (dj)][cB + (di)]) \
+#define TAU(buf, ff, cc, di, dj) (fene ? (((cc) == 0 || (cc) == 3 || (cc) == 5) \
+                                      ? fma(S.F[ff][rV + (dj)][cV + (di)], S.B[buf][cc][rB + (dj)][cB + (di)], S.F[ff][rV + (dj)][cV + (di)] - C.a_fene) \
+                                      : S.F[ff][rV + (dj)][cV + (di)] * S.B[buf][cc][rB + (dj)][cB + (di)]) \
                                        : S.B[buf][cc][rB + (dj)][cB + (di)])
         // sum of an off-diagonal component of the cell and of its neighbour
 #define TSUM(buf, ff, cc, di, dj) (fene ? fma(S.F[ff][rV + (dj)][cV + (di)], S.B[buf][cc][rB + (dj)][cB + (di)], S.F[ff][rV][cV] * S.B[buf][cc][rB][cB]) \
                                         : S.B[buf][cc][rB][cB] + S.B[buf][cc][rB + (dj)][cB + (di)])
-        // stress over G of plane k (TK) and of plane k+1 (TP); the constant -a of the FENE-P
-        // diagonal cancels in the differences
+        // stress over G of plane k (TK) and of plane k+1 (TP): F (B - I), and F - a on the FENE-P diagonal
+        // (not F B - a: B itself in 32 bits has lost the digits of a small B - I)
 #define TK(cc, di, dj) TAU(cur, f0, cc, di, dj)
 #define TP(cc, di, dj) TAU(nxt, f1, cc, di, dj)
         T u0, v0, w0;
