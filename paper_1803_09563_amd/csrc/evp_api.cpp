@@ -162,8 +162,11 @@ template <typename T> void stage_constants(evp::StageConst<T>& k, const Desc& h)
     k.qx = (T)(0.25 * h.idx); k.qy = (T)(0.25 * h.idy); k.qz = (T)(0.25 * h.idz);
     k.idx2 = (T)(h.idx * h.idx); k.idy2 = (T)(h.idy * h.idy); k.idz2 = (T)(h.idz * h.idz);
     k.e2x = (T)(1e-6 * h.dx * h.dx); k.e2y = (T)(1e-6 * h.dy * h.dy); k.e2z = (T)(1e-6 * h.dz * h.dz);
-    k.G = (T)h.G; k.L2 = (T)h.L2; k.a_fene = (T)h.a_fene; k.inv_lam = (T)h.inv_lam; k.tau_y = (T)h.tau_y;
+    k.G = (T)h.G; k.L2 = (T)h.L2; k.a_fene = (T)h.a_fene; k.inv_lam = (T)h.inv_lam;
     k.mu_s = (T)h.mu_s; k.inv_rho = (T)h.inv_rho; k.kappa = (T)h.kappa;
+    int e = 0;
+    k.G_unit = (T)std::frexp(h.G, &e);
+    k.tau_y_unit = (T)std::ldexp(h.tau_y, -e);
 }
 
 int upload_desc(evp_grid* g)

@@ -13,7 +13,8 @@ namespace evp {
 // mirrored in the host-side grid; kernels read it through a uniform pointer (scalar loads).
 template <typename T> struct StageConst {
     T idx, idy, idz, qx, qy, qz, idx2, idy2, idz2, e2x, e2y, e2z;   // 1/h, 1/(4h), 1/h^2 and 1e-6 h^2 per direction
-    T G, L2, a_fene, inv_lam, tau_y, mu_s, inv_rho, kappa;
+    T G, L2, a_fene, inv_lam, mu_s, inv_rho, kappa;
+    T G_unit, tau_y_unit;                                   // G and tau_y over the power of two next above G
 };
 
 struct Desc {

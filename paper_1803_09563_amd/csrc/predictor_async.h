@@ -90,7 +90,7 @@ template <typename T> __device__ __forceinline__ const __attribute__((address_sp
     const auto& C = constants<T>(again(Dp));                                                       \
     [[maybe_unused]] const T idx = C.idx, idy = C.idy, idz = C.idz, qx = C.qx, qy = C.qy, qz = C.qz; \
     [[maybe_unused]] const T idx2 = C.idx2, idy2 = C.idy2, idz2 = C.idz2, e2x = C.e2x, e2y = C.e2y, e2z = C.e2z; \
-    [[maybe_unused]] const T G = C.G, L2 = C.L2, il = C.inv_lam, tyld = C.tau_y, ms = C.mu_s, irho = C.inv_rho
+    [[maybe_unused]] const T G = C.G, L2 = C.L2, il = C.inv_lam, ms = C.mu_s, irho = C.inv_rho
 // a wave-uniform pointer, in scalar registers
 __device__ __forceinline__ gptr<const double> uniform(gptr<const double> p)
 {
@@ -471,12 +471,15 @@ __device__ __forceinline__ void march(SmemA<T, TX, TY, MODEL == EVP_FENE_P>& S, 
                 F = S.F[k & 1][rV][cV];
                 a = C.a_fene;
             } else if (sara) {
-                const T t3 = G * (bt[0] + bt[3] + bt[5]) * (T)(1.0 / 3.0);
-                const T dxx = G * bt[0] - t3, dyy = G * bt[3] - t3, dzz = G * bt[5] - t3;
-                const T txy = G * bt[1], txz = G * bt[2], tyz = G * bt[4];
+                // in units of a power of two near G, so that no choice of units brings the squares near the
+                // ends of the type's range (the yield factor is a ratio of stresses)
+                const T g = C.G_unit, tyld = C.tau_y_unit;
+                const T t3 = g * (bt[0] + bt[3] + bt[5]) * (T)(1.0 / 3.0);
+                const T dxx = g * bt[0] - t3, dyy = g * bt[3] - t3, dzz = g * bt[5] - t3;
+                const T txy = g * bt[1], txz = g * bt[2], tyz = g * bt[4];
                 const T n2 = (T)0.5 * (dxx * dxx + dyy * dyy + dzz * dzz) + txy * txy + txz * txz + tyz * tyz;
-                // 1 - tau_y / |tau_d| above the yield stress
-                F = n2 > tyld * tyld ? (T)1 - tyld * fast_rsqrt(n2) : (tyld == (T)0 ? (T)1 : (T)0);
+                // 1 - tau_y / |tau_d| above the yield stress; rounding leaves it in [0, 1]
+                F = n2 > tyld * tyld ? min(max((T)1 - tyld * fast_rsqrt(n2), (T)0), (T)1) : (tyld == (T)0 ? (T)1 : (T)0);
                 a = F;
             } else if (neo) {
                 F = (T)0;

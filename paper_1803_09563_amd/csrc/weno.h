@@ -21,8 +21,8 @@ __device__ __forceinline__ float fast_rcp(float a)
     float x = __builtin_amdgcn_rcpf(a);
     return fmaf(x, fmaf(-a, x, 1.0f), x);
 }
-// reciprocal square root of a >= 0, the argument limited to the normal numbers (so that 0 and infinity
-// give finite results): the hardware estimate refined by one step x <- x + x e / 2 (+ 3 x e^2 / 8 in
+// reciprocal square root of a >= 0, the argument limited to 2^-1000 .. 2^1000 and 2^-120 .. 2^120 (so that
+// 0 and infinity give finite results): the hardware estimate refined by one step x <- x + x e / 2 (+ 3 x e^2 / 8 in
 // FP64), e = 1 - a x^2.  1 - t fast_rsqrt(a) over a = t^2 .. 10^12 t^2 is off by at most 1.2e-16 and
 // 6.6e-8 (1 - t / sqrt(a): 1.4e-16 and 7.5e-8) and takes a third of the instructions.
 __device__ __forceinline__ double fast_rsqrt(double a)

@@ -1,4 +1,5 @@
-"""Stresses far from 1: conformation tensors within 1e-7 of the identity."""
+"""Stresses far from 1: conformation tensors within 1e-7 of the identity, and units in which the stress
+and its yield value are very small or very large."""
 import numpy as np
 import pytest
 
@@ -39,3 +40,23 @@ def test_small_fene_p_stresses_keep_their_digits(shape, walls):
     for k in ("u", "v", "w"):
         err = np.abs(got[k] - ref[k]).max() / np.abs(ref[k]).max()
         assert err <= 1e-2, (k, err)
+
+
+# The yield factor depends on the ratio of stress and yield stress alone, in any units whose squares are
+# representable.  The squares of 1e-19 (32 bits) and 1e-155 (64 bits) are subnormal: their sum is good to
+# 1e-5 and 3e-12 there, F to half of that, times dt |B| of up to 0.2; B itself is stored to 1e-7 and 1e-16.
+@pytest.mark.parametrize("precision,scale,tol", [("mixed", 1.0, 2e-6), ("mixed", 1e-19, 2e-6), ("mixed", 4e18, 2e-6),
+                                                 ("fp64", 1.0, 1e-12), ("fp64", 1e-155, 1e-12), ("fp64", 1e152, 1e-12)])
+def test_yield_factor_in_any_units(precision, scale, tol):
+    import paper_1803_09563_amd as evp
+    wl = _wl(16, 12, 10, False, "saramito")
+    wl.mu_s, wl.mu_p, wl.lam, wl.tau_y = 0.0, scale, 1.0, 0.3 * scale
+    u, v, w, B = inputs.random_state(wl.shape, 13, amp_u=0.0, amp_b=0.3)
+    s = oracle_solver(wl)
+    s.write_fields(u, v, w, B)
+    s.step(0.1, 1, flags=oracle.Solver.FREEZE_VELOCITY)
+    G = gpu_grid(wl, precision=evp.MIXED if precision == "mixed" else evp.FP64)
+    G.write_fields(*to_dev(u, v, w, B))
+    G.step(0.1, 1, flags=evp.FREEZE_VELOCITY)
+    d = np.abs(gpu_state(G, ("B",))["B"] - s.B).max()
+    assert 0.05 < np.abs(s.B - B).max() and d <= tol, (scale, d)
