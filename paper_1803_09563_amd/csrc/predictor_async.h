@@ -132,11 +132,12 @@ __device__ __forceinline__ void lds_barrier()
 // The cell's own values: raw buffer accesses at a wave-uniform plane base (descriptor in scalar
 // registers) plus the cell's byte offset in a plane, so that an access takes no vector arithmetic.
 // STREAM: data only this cell touches (history, results), non-temporal, so L2 keeps the halo lines.
-constexpr int kRawBufferWord3 = 0x00020000, kNonTemporal = 2;
+// A load at or past `bytes` touches no memory and gives 0.
+constexpr int kRawBufferWord3 = 0x00020000, kNonTemporal = 2, kAllBytes = 0x7fffffff;
 template <bool STREAM, typename T>
-__device__ __forceinline__ T ld_cell(gptr<const T> base, unsigned off)
+__device__ __forceinline__ T ld_cell(gptr<const T> base, unsigned off, int bytes = kAllBytes)
 {
-    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((EVP_GLOBAL void*)base, (short)0, 0x7fffffff, kRawBufferWord3);
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((EVP_GLOBAL void*)base, (short)0, bytes, kRawBufferWord3);
     if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, STREAM ? kNonTemporal : 0));
     else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, STREAM ? kNonTemporal : 0));
 }
@@ -144,7 +145,7 @@ template <typename T>
 __device__ __forceinline__ void st_stream(gptr<T> base, unsigned off, T v)
 {
     typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((EVP_GLOBAL void*)base, (short)0, 0x7fffffff, kRawBufferWord3);
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((EVP_GLOBAL void*)base, (short)0, kAllBytes, kRawBufferWord3);
     if constexpr (sizeof(T) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, 0, kNonTemporal);
     else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0, kNonTemporal);
 }
@@ -377,8 +378,9 @@ __device__ __forceinline__ void march(SmemA<T, TX, TY, MODEL == EVP_FENE_P>& S, 
     arrive<0>();
     __asm__ volatile("" : "+v"(note));
     round_v(k0 % 3);
-    // no history: none is taken, the histories' memory may hold anything
+    // no history: zeros are taken, the histories' memory may hold anything
     const bool none = euler || __builtin_amdgcn_readfirstlane(note) != 0;
+    const int hist_bytes = none ? 0 : kAllBytes;
     lds_barrier();
     // this launch writes the histories, so the note goes: at an Euler step, where no block reads it, at
     // once, otherwise when the last block has read it
@@ -581,9 +583,9 @@ __device__ __forceinline__ void march(SmemA<T, TX, TY, MODEL == EVP_FENE_P>& S, 
         {
             const CDesc& C = again(Dp);
 #pragma unroll
-            for (int cc = 0; cc < 3; ++cc) old[cc] = ld_cell<true, T>((gptr<const T>)C.RT + (kq + (C0 + cc) * ps), oT);
+            for (int cc = 0; cc < 3; ++cc) old[cc] = ld_cell<true, T>((gptr<const T>)C.RT + (kq + (C0 + cc) * ps), oT, hist_bytes);
 #pragma unroll
-            for (int f = 0; f < NF; ++f) oru[f] = ld_cell<true, T>((gptr<const T>)C.RU + (kq + (HALF + f) * ps), oT);
+            for (int f = 0; f < NF; ++f) oru[f] = ld_cell<true, T>((gptr<const T>)C.RU + (kq + (HALF + f) * ps), oT, hist_bytes);
         }
         // ---- second part: upper-convected terms, momentum (every lane; only valid cells are
         // stored).  e, w, n, s, f, b: the +x, -x, +y, -y, +z, -z neighbours ----
@@ -660,11 +662,11 @@ __device__ __forceinline__ void march(SmemA<T, TX, TY, MODEL == EVP_FENE_P>& S, 
                 // RK3 keeps the advection as the history; the stress divergence at B^k and any solid
                 // penalisation follow in k_stress_div
                 ru[0] = ax;
-                rs[0] = U0 + (double)(dt * (((T)2 * cal * (ms * lx + fx) + cal * tt) * irho - c1 * ax - (none ? (T)0 : c2 * oru[0])));
+                rs[0] = U0 + (double)(dt * (((T)2 * cal * (ms * lx + fx) + cal * tt) * irho - c1 * ax - c2 * oru[0]));
             } else {
                 // a solid, if any, is applied by k_penalise once u* is complete
                 ru[0] = -ax + (ms * lx + tt + fx) * irho;
-                rs[0] = U0 + (double)(dt * (c1 * ru[0] + (none ? (T)0 : c2 * oru[0])));
+                rs[0] = U0 + (double)(dt * fma(c1, ru[0], c2 * oru[0]));
             }
             if (freeze) { rs[0] = U0; ru[0] = (T)0; }
         } else {
@@ -699,13 +701,13 @@ __device__ __forceinline__ void march(SmemA<T, TX, TY, MODEL == EVP_FENE_P>& S, 
             if constexpr (RK3) {
                 ru[0] = ay;
                 ru[NF - 1] = az;
-                rs[0] = V0 + (double)(dt * (((T)2 * cal * (ms * ly) + cal * ty_) * irho - c1 * ay - (none ? (T)0 : c2 * oru[0])));
-                rs[NF - 1] = W0 + (double)(dt * (((T)2 * cal * (ms * lz) + cal * tz_) * irho - c1 * az - (none ? (T)0 : c2 * oru[NF - 1])));
+                rs[0] = V0 + (double)(dt * (((T)2 * cal * (ms * ly) + cal * ty_) * irho - c1 * ay - c2 * oru[0]));
+                rs[NF - 1] = W0 + (double)(dt * (((T)2 * cal * (ms * lz) + cal * tz_) * irho - c1 * az - c2 * oru[NF - 1]));
             } else {
                 ru[0] = -ay + (ms * ly + ty_) * irho;
                 ru[NF - 1] = -az + (ms * lz + tz_) * irho;
-                rs[0] = V0 + (double)(dt * (c1 * ru[0] + (none ? (T)0 : c2 * oru[0])));
-                rs[NF - 1] = W0 + (double)(dt * (c1 * ru[NF - 1] + (none ? (T)0 : c2 * oru[NF - 1])));
+                rs[0] = V0 + (double)(dt * fma(c1, ru[0], c2 * oru[0]));
+                rs[NF - 1] = W0 + (double)(dt * fma(c1, ru[NF - 1], c2 * oru[NF - 1]));
             }
             if (vwall) { rs[0] = 0.0; ru[0] = (T)0; }
             if (freeze) {
@@ -716,7 +718,7 @@ __device__ __forceinline__ void march(SmemA<T, TX, TY, MODEL == EVP_FENE_P>& S, 
         }
 #pragma unroll
         for (int cc = 0; cc < 3; ++cc) {
-            rb[cc] = wm[2][cc] + dt * (c1 * rt[cc] + (none ? (T)0 : c2 * old[cc]));
+            rb[cc] = wm[2][cc] + dt * fma(c1, rt[cc], c2 * old[cc]);
         }
         keep_v();
 #undef U0
