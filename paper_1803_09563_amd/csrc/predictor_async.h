@@ -108,10 +108,10 @@ __device__ __forceinline__ void load_lds(unsigned lds, gptr<const T> base, unsig
     static_assert(BYTES == 16 || BYTES == 4, "the widths below");
     if constexpr (BYTES == 16)
         __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2"
-                         ::"s"(lds), "v"(off), "s"(base) : "memory");
+                         ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
     else
         __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dword %1, %2"
-                         ::"s"(lds), "v"(off), "s"(base) : "memory");
+                         ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
 }
 // The requests of this wave have arrived.  vmcnt counts a wave's loads and stores in order; LATER of
 // them may still be in flight (issued after the requests).
