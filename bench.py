@@ -41,7 +41,7 @@ STEP_BYTES = {k: v + 32 + 48 + 72 for k, v in PRED_BYTES.items()}
 STRESS_DIV_BYTES = {"fp64": 6 * 8 + 48, "mixed": 6 * 4 + 48}
 
 PRED_SOURCES = [os.path.join(HERE, "paper_1803_09563_amd", "csrc", f)
-                for f in ("predictor_async.h", "weno.h")]
+                for f in ("predictor_async.h", "weno.h", "k_predictor_fp64.hip", "k_predictor_mixed.hip")]
 # rocprofv3 summaries of the predictor on the headline workload: HBM bytes per launch
 # (FETCH_SIZE / WRITE_SIZE) and SQ counters, each tagged with the kernel sources' hash
 TRAFFIC_FILE = os.path.join(HERE, "profiles", "predictor_channel512_hbm_traffic.txt")
@@ -52,7 +52,8 @@ RHEOLOGY_TEXT = {"kolmogorov128": "Saramito Wi=1 Bi=0.5 beta=0.5 Re=1000",
 
 
 def pred_source_hash():
-    """sha256[:16] of the predictor's sources (kernel file and its WENO header, concatenated)."""
+    """sha256[:16] of the predictor's sources (the kernel, its WENO header and the two files with its
+    launches, whose tiles and chunks shape its traffic; concatenated)."""
     import hashlib
     h = hashlib.sha256()
     for f in PRED_SOURCES:
