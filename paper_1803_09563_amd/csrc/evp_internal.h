@@ -9,14 +9,15 @@
 
 namespace evp {
 
-// Per-grid constants and pointers.  Lives at the start of the grid's workspace (device) and is
-// mirrored in the host-side grid; kernels read it through a uniform pointer (scalar loads).
+// Constants of the predictor's stages in the type of its arithmetic.
 template <typename T> struct StageConst {
     T idx, idy, idz, qx, qy, qz, idx2, idy2, idz2, e2x, e2y, e2z;   // 1/h, 1/(4h), 1/h^2 and 1e-6 h^2 per direction
     T G, L2, a_fene, inv_lam, mu_s, inv_rho, kappa;
     T G_unit, tau_y_unit;                                   // G and tau_y over the power of two next above G
 };
 
+// Per-grid constants and pointers.  Lives at the start of the grid's workspace (device) and is
+// mirrored in the host-side grid; kernels read it through a uniform pointer (scalar loads).
 struct Desc {
     int nx, ny, nz, nh;          // cells; nh = nx/2 + 1 complex values per x-spectrum line
     int walls;                   // EVP_WALLS in y?

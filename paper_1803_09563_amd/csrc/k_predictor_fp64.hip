@@ -4,12 +4,12 @@
 namespace evp {
 
 // Tiles: 32 x 8 cells (two blocks per CU by their LDS) or 16 x 8 (three).  The wide tile reads less
-// halo per cell and is the faster one where both fill the chip alike (128^3 Saramito: 169 against
-// 176 us; 512x256x256: 2567 against 2718 us); the narrow one wastes fewer columns of widths that are
-// no multiple of 32 and gives small grids more blocks (48^3: 20 against 26 us).  A plane of the chip
-// takes 1.3 times as long in wide tiles (512 x 256 cells against 768 x 128).  FENE-P stages its factor
-// too, with which two wide tiles do not fit a CU's LDS: always narrow (512x256x256: 2740 against
-// 3040 us).
+// halo per cell and is the faster one where both fill the chip alike (128^3 Saramito: 175 against
+// 179 us; 512x256x256: 2550 against 2900 us); the narrow one wastes fewer columns of widths that are
+// no multiple of 32 and gives small grids more blocks (48^3: 21 against 27 us; 32^3: 12 against 14).  A
+// plane of the chip takes 1.3 times as long in wide tiles (512 x 256 cells against 768 x 128).  FENE-P
+// stages its factor too, with which two wide tiles do not fit a CU's LDS: always narrow (512x256x256: 2710
+// against 2965 us; 96x400x64: 230 against 260).
 hipError_t launch_predictor_fp64(const Batch& b, int nx, int ny, int nz, bool freeze, hipStream_t s, int model, bool rk3, bool houc)
 {
     const int fz = freeze ? 1 : 0;

@@ -8,9 +8,9 @@
 // multiple of 8 values, 128 bytes):
 //   periodic: div+fft(x) | fft(y) | fft(z), divide, ifft(z) | ifft(y) | ifft(x) -> p | correct
 //   walls:    div+fft(x) | fft(z) | Thomas(y)                | ifft(z) | ifft(x) -> p | correct
-// Real x-lines are transformed two at a time as one complex line (a + i b).  Periodic batches of
-// nx == ny <= 128 with enough z planes to fill the chip fuse the first two and the last two
-// periodic passes into one block per z plane, whose half-spectrum plane stays in LDS.
+// Real x-lines are transformed two at a time as one complex line (a + i b).  Periodic grids with
+// nx == ny up to 64, and 96 or 128 in batches with a z plane for every CU, fuse the first two and the last
+// two periodic passes into one block per z plane, whose half-spectrum plane stays in LDS.
 #include "evp_internal.h"
 #include "fft_lds.h"
 

@@ -535,7 +535,7 @@ __device__ __forceinline__ void march(SmemA<T, TX, TY, MODEL == EVP_FENE_P>& S, 
         {
             EVP_STAGE_CONSTANTS;
             const T kap = C.kappa;
-            // local artificial diffusion (Sec. (T)3.1): det B < 0, or tr B >= (T)0.95 L^2 (FENE-P)
+            // local artificial diffusion (Sec. 3.1): det B < 0, or tr B >= 0.95 L^2 (FENE-P)
             if (kap > (T)0) {
                 T bt[6];
 #pragma unroll
@@ -740,9 +740,11 @@ __device__ __forceinline__ void march(SmemA<T, TX, TY, MODEL == EVP_FENE_P>& S, 
 constexpr int kAnyModel = -1;      // several models in one launch
 
 // Waves per SIMD the registers are to allow.  Mixed form, wide tiles: three blocks fit a CU's LDS, and six
-// waves in 80 registers (a few spilled) beat four in 90 where a grid fills them (512x256x256 Saramito:
-// 1446 against 1580 us; 128^3: 105 against 107); FENE-P, with 20 spilled, gains nothing (256x128x128: 248
-// against 232 us).
+// waves in 80 registers (7 to 12 spilled) beat four in 90 where a grid fills them (512x256x256 Saramito:
+// 1446 against 1580 us; 128^3: 105 against 107); FENE-P alone, with 28 spilled, loses (256x128x128: 249
+// against 222 us).  The kernel for several models gains although it holds the FENE-P march (61 spilled, 84
+// bytes of scratch a lane; none at four waves): 16 grids of 48^3, a third of them FENE-P, 123 against 139
+// us, 32 of 32^3 66 against 73, 16 of 64^3 227 against 246, 8 of 96^3 386 against 400.
 template <typename T, int TX, int MODEL> constexpr int min_waves()
 {
     return sizeof(T) == 4 && TX == 32 && MODEL != EVP_FENE_P ? 6 : 4;
