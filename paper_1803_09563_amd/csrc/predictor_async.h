@@ -22,8 +22,8 @@
 // for the update of the plane after.
 //
 // What bounds it: in FP64 at 512x256x256 the vector ALU (1.4k instructions per cell and plane, busy 0.6 of
-// the cycles at the 2.1 GHz the chip holds under this load) and memory (12.5 GB a launch, 5.0 TB/s, above a
-// plain copy's 4.8) are about equal, and neither hides fully behind the other.  The mixed form is bound by
+// the cycles at the 2.1 GHz the chip holds under this load) and memory (12.3 GB a launch, 4.9 TB/s, a plain
+// copy's rate) are about equal, and neither hides fully behind the other.  The mixed form is bound by
 // the vector ALU (1.4k instructions, FP32 runs at the rate of FP64 here; busy all the time).  Against the synchronously
 // staged form before it (one thread per cell, FP64: two waves per SIMD and three exposed memory round
 // trips a plane; mixed: four waves, the rows beside a wall in a kernel of their own on a second stream):
@@ -740,7 +740,7 @@ __device__ __forceinline__ void march(SmemA<T, TX, TY, MODEL == EVP_FENE_P>& S, 
 constexpr int kAnyModel = -1;      // several models in one launch
 
 // Waves per SIMD the registers are to allow.  Mixed form, wide tiles: three blocks fit a CU's LDS, and six
-// waves in 80 registers (7 to 12 spilled) beat four in 90 where a grid fills them (512x256x256 Saramito:
+// waves in 80 registers (10 to 12 spilled) beat four in 90 where a grid fills them (512x256x256 Saramito:
 // 1446 against 1580 us; 128^3: 105 against 107); FENE-P alone, with 28 spilled, loses (256x128x128: 249
 // against 222 us).  The kernel for several models gains although it holds the FENE-P march (61 spilled, 84
 // bytes of scratch a lane; none at four waves): 16 grids of 48^3, a third of them FENE-P, 123 against 139
