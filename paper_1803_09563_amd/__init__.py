@@ -211,20 +211,24 @@ class Grid:
                 buf.record_stream(stream)
         self.stream = stream
 
-    def _hand_over(self, tensors):
-        """Order the caller's current stream after the grid's, which fills these tensors of its own,
-        and keep their memory from the grid's later reads until the current stream is done with them.
+    def _caller(self):
+        """The caller's current stream if it is not the grid's own, else None."""
+        cur = _torch().cuda.current_stream(self.device)
+        return None if cur == self.stream else cur
+
+    def _hand_over(self, caller, tensors):
+        """Order the caller's stream after the grid's, which fills these tensors of its own, and keep
+        their memory from the grid's later reads until the caller's stream is done with them.
         Streams under capture are left to the capture, which orders its own forks and joins."""
         torch = _torch()
-        cur = torch.cuda.current_stream(self.device)
-        if cur == self.stream or torch.cuda.is_current_stream_capturing():
+        if caller is None or torch.cuda.is_current_stream_capturing():
             return
         with torch.cuda.stream(self.stream):
             if torch.cuda.is_current_stream_capturing():
                 return
-        cur.wait_stream(self.stream)
+        caller.wait_stream(self.stream)
         for t in tensors:
-            t.record_stream(cur)
+            t.record_stream(caller)
 
     def set_rheology(self, model, rho=1.0, mu_s=0.0, mu_p=0.0, lam=1.0, tau_y=0.0, L2=1.0e4):
         _check(lib.evp_set_rheology(self._h, int(model), rho, mu_s, mu_p, lam, tau_y, L2),
@@ -277,10 +281,11 @@ class Grid:
 
     def read_level_set(self):
         torch = _torch()
-        with torch.cuda.stream(self.stream):
+        caller = self._caller()
+        with torch.cuda.stream(self.stream if caller is not None else None):
             out = torch.empty(self.shape, dtype=torch.float64, device=self.device)
         _check(lib.evp_read_level_set(self._h, ctypes.c_void_p(out.data_ptr())), "evp_read_level_set")
-        self._hand_over([out])
+        self._hand_over(caller, [out])
         return out
 
     def set_forcing(self, kind, amp=0.0, ky=0.0):
@@ -314,7 +319,8 @@ class Grid:
         out = {}
         mask = 0
         bits = {"u": READ_U, "v": READ_V, "w": READ_W, "p": READ_P, "B": READ_B, "hist": READ_HIST}
-        with torch.cuda.stream(self.stream):
+        caller = self._caller()
+        with torch.cuda.stream(self.stream if caller is not None else None):
             for k in which:
                 shp = (6,) + s if k == "B" else (9,) + s if k == "hist" else s
                 out[k] = torch.empty(shp, dtype=torch.float64, device=self.device)
@@ -322,19 +328,20 @@ class Grid:
         ptr = lambda k: ctypes.c_void_p(out[k].data_ptr()) if k in out else None
         _check(lib.evp_read_fields(self._h, mask, ptr("u"), ptr("v"), ptr("w"), ptr("p"),
                                    ptr("B"), ptr("hist")), "evp_read_fields")
-        self._hand_over(out.values())
+        self._hand_over(caller, out.values())
         return out
 
     def save_state(self):
         """Bitwise checkpoint of the state in a device uint8 tensor."""
         torch = _torch()
         n = int(lib.evp_state_bytes(self._h))
-        with torch.cuda.stream(self.stream):
+        caller = self._caller()
+        with torch.cuda.stream(self.stream if caller is not None else None):
             buf = torch.empty(n + 256, dtype=torch.uint8, device=self.device)
         off = (-buf.data_ptr()) % 256
         view = buf[off:off + n]
         _check(lib.evp_save_state(self._h, ctypes.c_void_p(view.data_ptr()), n), "evp_save_state")
-        self._hand_over([buf])
+        self._hand_over(caller, [buf])
         return view
 
     def load_state(self, state):
